@@ -17,7 +17,8 @@
  *              (origin on the optical axis, every pixel counts, x along columns).
  *   Output     phases in [0, 2 pi] (float rounding can return 2 pi itself);
  *              V as interleaved (re, im) float pairs.
- *   Precision  FP32 on the device; per-trap coefficients are formed in FP64 on
+ *   Precision  FP32 on the device (matrix products of FP32 accuracy from pairs of halves, see
+ *              enum hot_variant); per-trap coefficients are formed in FP64 on
  *              the host and rounded once.  Inside the iterative solvers the per-block
  *              trap sums of Eq. 1 are rounded to fixed point, 2^-30 in units of V
  *              (re and im as 32-bit integers packed into one 64-bit atomic add), so
@@ -78,13 +79,19 @@ enum hot_status {
   HOT_EDEGENERATE = -4  /* GSW/GS met <|V|> = 0: the phase mask sends no light to any trap */
 };
 
-/* How the propagation phase Delta is obtained inside the two passes. */
+/* How the propagation phase Delta is obtained inside the two passes.
+ * The on-the-fly (default) and the separable variant both run on the tile kernels: for each tile of
+ * pixels the two factors of exp(i Delta) = X_m(column) Y_m(row), exact for Eq. 2, are recomputed with
+ * FP32 sin/cos and contracted on the FP16 matrix cores, every factor carried as a pair of halves
+ * (22 bits and more) and summed in FP32: the accuracy of FP32 products.  Setting a launch-shape knob of
+ * a variant's other kernels (hot_set_tuning) selects those instead. */
 enum hot_variant {
-  HOT_ONTHEFLY = 0, /* Delta recomputed per (pixel, trap) with FP32 sin/cos (default) */
+  HOT_ONTHEFLY = 0, /* Delta recomputed on the fly (default).  With a knob of the direct sums set: per
+                       (pixel, trap), with FP32 sin/cos for every term */
   HOT_STORED = 1,   /* exp(i Delta) precomputed once as a complex64 [M][N] matrix, then two GEMV-shaped passes */
-  HOT_SEPARABLE = 2 /* exact factorisation of Eq. 2, exp(i Delta) = X_m(column) Y_m(row): both passes become
-                       dense complex contractions on the FP32 matrix cores, fused into one kernel per
-                       iteration, with O((nx+ny) M) tables; also used by the batched, Eq. 1 and adjoint calls */
+  HOT_SEPARABLE = 2 /* exact factorisation of Eq. 2, exp(i Delta) = X_m(column) Y_m(row), in dense complex
+                       contractions; also used by the batched, Eq. 1 and adjoint calls.  With a HOT_TUNE_SEP
+                       knob set: on the FP32 matrix cores */
 };
 
 /* ---- context ------------------------------------------------------------------------ */
@@ -103,7 +110,10 @@ int hot_set_stream(hot_ctx* ctx, void* stream);
 int hot_set_variant(hot_ctx* ctx, int variant);
 /* Launch-shape knobs (used by the autotuner; 0 restores the built-in choice, except
  * HOT_TUNE_GRAPHS).  They change how work is tiled or launched, never what is computed
- * beyond FP32 summation order. */
+ * beyond FP32 rounding.  With every knob of a variant at 0 it runs on the tile kernels, which choose
+ * their own shapes; a HOT_TUNE_SEP knob selects the FP32 matrix kernels of the separable variant, any
+ * other knob (but HOT_TUNE_GRAPHS) the direct-sum kernels of the on-the-fly variant, and the built-in
+ * choices named below are those kernels' own. */
 enum hot_tuning_key {
   HOT_TUNE_PIXELS_PER_LANE = 1, /* fused iteration kernel: pixels per lane, 1 or 2 */
   HOT_TUNE_TRAPS_PER_LANE = 2,  /* trap pass: traps each lane accumulates: 1..6 or 8 */
@@ -177,7 +187,7 @@ int hot_gsw(hot_ctx* ctx, const hot_slm* slm, int32_t M, const double* xyz, cons
  * launched eagerly; bit for bit the result of hot_gsw with the context's launch shape.  It calls
  * no hipMalloc, hipFree or other allocating routine: every device table, state, trap sum,
  * statistic and flag it needs lives in a fixed 1 MiB workspace per GPU (a file-scope device array
- * whose address hot_create looks up), and its host tables go through a pinned staging buffer that
+ * whose address hot_create looks up, with a further 1 MiB for the trap fields of the last masks), and its host tables go through a pinned staging buffer that
  * hot_create allocates.  Limit: the workspace holds M traps and `iters` iterations when its six
  * regions, 32 M (coefficients) + 32 M (state) + 64 (descriptors) + 192 M (trap sums) +
  * 12 (iters + 1) (statistics) + 4 (flag) bytes, each rounded up to a multiple of 256, total at most
@@ -228,10 +238,9 @@ int hot_encode_u8(hot_ctx* ctx, int64_t n, const float* phase, uint8_t* frame);
  * launches four groups of kernels `reps` times each, back to back on the context's stream
  * (current variant and tuning), each group bracketed by HIP events, and writes the mean
  * device time per launch in milliseconds to
- *   ms[0]  one GSW iteration's main work (on-the-fly: the fused update + pixel pass + trap pass
- *          kernel, which also sums the trap pass into V's fixed-point accumulators; separable:
- *          the fused update + both passes on the matrix cores; stored: the pixel and trap
- *          pass kernels)
+ *   ms[0]  one GSW iteration's main work (on-the-fly and separable: the fused update + pixel pass
+ *          + trap pass kernel, which also sums the trap pass into V's fixed-point accumulators;
+ *          stored: the pixel and trap pass kernels)
  *   ms[1]  the reduction into V (stored: of the per-block partials, once per iteration;
  *          on-the-fly and separable: of the fixed-point accumulators, once per solve)
  *   ms[2]  the pixel pass alone   ms[3]  the trap pass alone

@@ -13,7 +13,8 @@ For one problem shape it times every candidate combination of
     rows             (rows per block, 1 or 2: two rows share one update and one set of trap sums)
 
 with ``hot_time_passes`` (HIP events around back-to-back launches on the context's stream),
-keeps the fastest fused-iteration kernel, and caches it in a JSON file keyed by
+beside the library's own choice (every knob 0: the tile kernels; any of these knobs selects the
+direct-sum kernels), keeps the fastest fused-iteration kernel, and caches it in a JSON file keyed by
 (architecture, variant, grid, trap-count bucket).  The sweep table doubles as an
 ablation of the kernel's shape choices on this GPU.  Only launch shapes change --
 results differ at most by FP32 summation order.
@@ -51,11 +52,12 @@ def cache_key(ctx: Context, slm, m: int, variant: str = "onthefly") -> str:
 
 
 def sweep(ctx: Context, slm, xyz, theta0, reps: int = 20, candidates: Optional[dict] = None) -> list:
-    """Time every knob combination; returns rows sorted by the fused-iteration time."""
+    """Time every knob combination (and, without `candidates`, the library's own choice); returns rows
+    sorted by the fused-iteration time."""
     cand = candidates or CANDIDATES
     rows = []
-    for q, seg, tpl, nr in itertools.product(cand["pixels_per_lane"], cand["segment"], cand["traps_per_lane"],
-                                             cand.get("rows", (1,))):
+    shapes = itertools.product(cand["pixels_per_lane"], cand["segment"], cand["traps_per_lane"], cand.get("rows", (1,)))
+    for q, seg, tpl, nr in itertools.chain(() if candidates else ((0, 0, 0, 0),), shapes):
         if seg == 256 and q == 2:
             continue  # same launch as (q=1, seg=256)
         if nr == 2 and q == 1 and seg != 256 and int(slm.nx) > 256:
@@ -122,7 +124,8 @@ def sweep_batched(ctx: Context, slm, counts, xyz, theta0, iters: int = 2, reps: 
     phase = torch.empty(B, int(slm.ny), int(slm.nx), device=ctx.device)
     V = torch.empty(T, 2, device=ctx.device)
     rows = []
-    for tpl, nr, q in itertools.product(cand["traps_per_lane"], cand["rows"], cand["pixels_per_lane"]):
+    shapes = itertools.product(cand["traps_per_lane"], cand["rows"], cand["pixels_per_lane"])
+    for tpl, nr, q in itertools.chain(() if candidates else ((0, 0, 0),), shapes):  # (0, 0, 0): the library's choice
         try:
             ctx.set_tuning(traps_per_lane=tpl, rows=nr, pixels_per_lane=q)
             run = lambda: ctx.hot_gsw_batched(slm, cnt, xyz, theta0, iters, phase=phase, V=V, stats=False)

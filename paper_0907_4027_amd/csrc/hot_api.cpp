@@ -57,6 +57,9 @@ constexpr int kRing = 8;
 // captured launch sequences kept per context (least recently used dropped first): enough for a
 // batch of holograms solved one by one into their own output buffers
 constexpr int kGraphCache = 128;
+// masks whose V is kept before their figures of merit are taken, and the memory that may take
+constexpr int kHistMasks = 64;
+constexpr int64_t kHistBytes = int64_t(64) << 20;
 constexpr double kPi = 3.14159265358979323846;
 
 }  // namespace
@@ -81,6 +84,7 @@ struct hot_ctx {
   uint64_t graph_clock = 0;
   DevBuf coef, st, hd, partial, stats, flag, amat, efield;
   DevBuf probe;  // micro-benchmark sink and clock stamps
+  DevBuf hist;   // tile kernels: V of the last masks of a solve, for their figures of merit
   DevBuf abl;    // per-block records of the pixel-pass ablation
   DevBuf acc;  // fused paths: 3 rotating buffers of fixed-point trap sums [kAccRegions][T] u64 (re + 2^32 im)
   Staging ring[kRing];
@@ -258,6 +262,9 @@ struct Plan {
   int nblk_stored = 0;
   // separable variant: blocks of 16 rows x 16 sep_w columns, sep_sc traps per LDS super-chunk
   int sep_w = 4, nblk_sep = 0, sep_sc = 16;
+  // tile kernels: whether they run, block shape (index into kTileShapes), traps per LDS super-chunk
+  bool tiles = false;
+  int tile = 0, tile_mc = 16, nblk_tile = 0;
   int sep_kh = 1;  // waves per 16 x 16 tile in the separable iteration (2: each takes half of the traps)
   // fused paths' fixed point: scale 2^s with s = 30 - ceil(log2 N) (re and im as 32-bit integers in
   // one 64-bit word); every block sum and every trap's total has magnitude <= N, so no sum of the
@@ -275,11 +282,51 @@ FwdGeom row_segments(int nx, int ny, int segmax) {
   return f;
 }
 
+// Whether the on-the-fly or separable variant runs on the tile kernels: always, unless a launch-shape
+// knob of that variant's other kernels is set (the direct-sum kernels' for the on-the-fly variant, the
+// FP32 matrix kernels' for the separable one), which selects those.
+bool use_tiles(const hot_ctx* c, int variant) {
+  if (variant == HOT_STORED) return false;
+  if (variant == HOT_SEPARABLE) return !c->tune_sepw && !c->tune_sepc && !c->tune_sepk;
+  return !c->tune_q && !c->tune_tpl && !c->tune_seg && !c->tune_amax && !c->tune_rows && !c->tune_fract;
+}
+
+// Block shape and super-chunk of the tile kernels.
+//   64 x 64 pixels (8 waves) once such blocks number at least half of the compute units: their table
+//   work per pixel is half of a 32 x 32 block's (GSW 1024^2 x 256: 24.8 against 42.7 us per iteration;
+//   768^2 x 81, 144 blocks: 15.1 against 20.5 us), while a grid with fewer leaves units idle (512^2 x
+//   100, 64 blocks: 12.2 against 7.5 us).
+//   Else 32 x 32: four waves, or eight (two sharing each 16 x 16 tile, half of the traps each) for more
+//   than 48 traps on a grid of at most one block per unit, where a second wave per SIMD hides latency
+//   (512^2 x 100: 7.5 against 8.2 us); with fewer traps or two resident blocks the exchange of the
+//   partial sums costs more than it hides (641 x 479 x 37: 12.8 against 12.4 us).
+// All traps at once where their tables fit the LDS; on a grid of more blocks than units half of the LDS,
+// so that two blocks share a unit and one's table building overlaps the other's matrix products
+// (2048^2 x 1000: 307 against 340 us per iteration, 64 holograms of 512^2: 222 against 259 us).
+void choose_tile(const hot_ctx* c, Plan& P) {
+  auto blocks = [&](int shape) { return (int64_t)kTileShapes[shape].gx(P.nx) * kTileShapes[shape].gy(P.ny) * P.B; };
+  if (2 * blocks(kTile64) >= c->num_cu) {
+    P.tile = kTile64;
+  } else {
+    P.tile = P.mmax > 48 && blocks(kTile32) <= c->num_cu ? kTile32Split : kTile32;
+  }
+  const TileShape& t = kTileShapes[P.tile];
+  P.nblk_tile = t.gx(P.nx) * t.gy(P.ny);
+  const int mp = (P.mmax + 15) / 16 * 16;
+  const size_t budget = (size_t)kLdsMax / (blocks(P.tile) > c->num_cu ? 2 : 1);
+  int mc = mp;
+  while (mc > 16 && tile_lds_bytes(t, mc, P.mmax) > budget) mc -= 16;
+  const int nsc = (mp + mc - 1) / mc;  // equal super-chunks
+  P.tile_mc = ((mp + nsc - 1) / nsc + 15) / 16 * 16;
+}
+
 // Build the coefficient, state and descriptor tables of a problem on the host, into coef_out [T],
-// st_out [T] and hd_out [2B] (the fused kernel's layouts, then the stand-alone trap pass's).
-int prepare_into(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const double* xyz,
+// st_out [T] and hd_out [2B] (the fused kernel's layouts, then the stand-alone trap pass's; without
+// lane layouts when `variant` runs on the tile kernels, which need none).
+int prepare_into(hot_ctx* c, int variant, const hot_slm* slm, int B, const int32_t* counts, const double* xyz,
                  const double* theta0, bool seeded, uint64_t seed, Plan& P, TrapCoef* coef_out, TrapState* st_out,
                  HoloDesc* hd_out) {
+  P.tiles = use_tiles(c, variant);
   P.B = B;
   P.nx = slm->nx;
   P.ny = slm->ny;
@@ -372,6 +419,8 @@ int prepare_into(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, c
     P.sep_sc = std::max(16, sc);
   }
 
+  choose_tile(c, P);
+
   // Eq. 2 in revolutions per pixel-index unit (hot_internal.h), in FP64; a and b are reduced to
   // [-1/2, 1/2] (exact: U and V are integers, so a U and b V change by whole revolutions)
   const double lf = slm->wavelength * slm->focal;
@@ -404,6 +453,16 @@ int prepare_into(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, c
     s.w = 1.0f;
     s.pad = 0.0f;
     st_out[t] = s;
+  }
+  if (P.tiles) {
+    for (int b = 0, off = 0; b < B; off += counts[b++]) {
+      HoloDesc h{};
+      h.m = counts[b];
+      h.off = off;
+      hd_out[b] = hd_out[B + b] = h;
+    }
+    P.one = hd_out[0];
+    return HOT_OK;
   }
   // Largest per-term argument of the direct passes, |g u^2 + a' u + C| with |a'| <= min(1/4, |a| + 2|g| Uc)
   // (a' is reduced mod 1/2), |C| < 3/2 and |u| at most the widest block of any pass in U units (the
@@ -448,14 +507,14 @@ int prepare_into(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, c
   return HOT_OK;
 }
 
-int prepare(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const double* xyz, const double* theta0,
+int prepare(hot_ctx* c, int variant, const hot_slm* slm, int B, const int32_t* counts, const double* xyz, const double* theta0,
             bool seeded, uint64_t seed, Plan& P) {
   int64_t T = 0;
   for (int b = 0; b < B; ++b) T += counts[b];
   c->h_coef.resize(T);
   c->h_st.resize(T);
   c->h_hd.resize(2 * (size_t)B);
-  return prepare_into(c, slm, B, counts, xyz, theta0, seeded, seed, P, c->h_coef.data(), c->h_st.data(),
+  return prepare_into(c, variant, slm, B, counts, xyz, theta0, seeded, seed, P, c->h_coef.data(), c->h_st.data(),
                       c->h_hd.data());
 }
 
@@ -475,6 +534,7 @@ int upload_tables(hot_ctx* c, const hot_slm* slm, const Plan& P, const double* x
   key.push_back(c->tune_seg);
   key.push_back(c->tune_amax);
   key.push_back(c->tune_sepw);
+  key.push_back(P.tiles);
   key.push_back(P.B);
   for (int b = 0; b < P.B; ++b) key.push_back(counts[b]);
   key.insert(key.end(), xyz, xyz + 3 * (size_t)P.T);
@@ -543,6 +603,14 @@ SepArgs sep_args(hot_ctx* c, const Plan& P, int mode, float* phase, int K) {
   return a;
 }
 
+// The same arguments for the tile kernels.
+SepArgs tile_args(hot_ctx* c, const Plan& P, int mode, float* phase, int K) {
+  SepArgs a = sep_args(c, P, mode, phase, K);
+  a.shape = P.tile;
+  a.sc = P.tile_mc;
+  return a;
+}
+
 // Buffer i (0..2) of the iteration kernels' rotating fixed-point sums.
 unsigned long long* acc_buf(hot_ctx* c, const Plan& P, int i) {
   return (unsigned long long*)c->acc.p + (size_t)i * kAccRegions * P.T;
@@ -578,16 +646,21 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   int rc;
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
+  if ((rc = prepare(c, variant, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
   const int K = algo == kRS ? 0 : iters;
   const bool stored = variant == HOT_STORED;
   const bool separable = variant == HOT_SEPARABLE;
+  const bool tiles = P.tiles;
   const int nblk = stored ? P.nblk_stored : separable ? P.nblk_sep : P.fg.nblk();
   if ((rc = upload_tables(c, slm, P, xyz, counts))) return rc;
   if (stored && (rc = ensure(c, c->partial, sizeof(float2) * (size_t)P.T * nblk))) return rc;
   if ((rc = ensure(c, c->stats, sizeof(float) * 3 * (size_t)B * (K + 1)))) return rc;
   if (stored && (rc = ensure_stored(c, P))) return rc;
   if (!stored && (rc = ensure_acc(c, P))) return rc;
+  // tile kernels: V of up to `ring` masks is kept, and their figures of merit taken together
+  const int ring = (int)std::max<int64_t>(1, std::min<int64_t>({K, kHistMasks, kHistBytes / (8 * (int64_t)P.T)}));
+  const bool want = tiles && stats && K > 0;
+  if (want && (rc = ensure(c, c->hist, sizeof(float2) * (size_t)ring * P.T))) return rc;
   TrapState* st[2] = {(TrapState*)c->st.p, (TrapState*)c->st.p + P.T};
   if (w0) HIP_TRY(launch_import_w(c->stream, w0, st[0], P.T));
 
@@ -600,9 +673,9 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   // The K-iteration launch sequence (one kernel per iteration on the fused paths, four on the stored one).
   auto enqueue = [&](hipStream_t s) -> hipError_t {
     hipError_t e = hipSuccess;
-    if (separable) {
+    if (separable || tiles) {
       // one launch per iteration, with the same rotation of fixed-point sums as the direct path
-      SepArgs a = sep_args(c, P, 0, phase, K);
+      SepArgs a = tiles ? tile_args(c, P, 0, phase, K) : sep_args(c, P, 0, phase, K);
       e = launch_fill_u32(s, (unsigned*)acc_buf(c, P, 1), 0u, 2 * kAccRegions * P.T);
       for (int k = 0; k <= K && e == hipSuccess; ++k) {
         a.upd = k == 0 ? 0 : upd;
@@ -613,7 +686,11 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
         a.acc_zero = acc_buf(c, P, (k + 2) % 3);
         a.kstat = k - 1;
         a.phase = k == K ? phase : nullptr;  // only the last mask's phase is returned
-        e = launch_sep(s, a);
+        const int slot = k > 0 ? (k - 1) % ring : 0;
+        if (want && k > 0) a.hist = (float2*)c->hist.p + (size_t)slot * P.T;
+        e = tiles ? launch_tile(s, a) : launch_sep(s, a);
+        if (e == hipSuccess && want && k > 0 && (slot == ring - 1 || k == K))
+          e = launch_stats(s, slot + 1, B, P.T, (const float2*)c->hist.p, hd, st[0], dstats, k - 1 - slot, K + 1);
       }
     } else if (!stored) {
       // one launch per iteration: launch k reads buffer k % 3, adds into (k + 1) % 3 (buffer 1 is
@@ -659,7 +736,7 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
     std::vector<uint64_t> key = {(uint64_t)B, (uint64_t)P.T, (uint64_t)P.nx, (uint64_t)P.ny, (uint64_t)K,
                                  (uint64_t)algo, (uint64_t)variant, (uint64_t)P.fract, (uint64_t)P.nt, (uint64_t)P.q,
                                  (uint64_t)P.tpl, (uint64_t)P.fg.seg_w, (uint64_t)P.sep_w, (uint64_t)P.sep_sc, (uint64_t)P.sep_kh,
-                                 (uint64_t)P.rows, (uint64_t)(uintptr_t)phase,
+                                 (uint64_t)P.rows, (uint64_t)tiles, (uint64_t)want, (uint64_t)(uintptr_t)c->hist.p, (uint64_t)P.tile, (uint64_t)P.tile_mc, (uint64_t)(uintptr_t)phase,
                                  (uint64_t)(uintptr_t)V, (uint64_t)(uintptr_t)w_out, (uint64_t)(uintptr_t)theta_out,
                                  (uint64_t)(uintptr_t)c->coef.p, (uint64_t)(uintptr_t)c->st.p,
                                  (uint64_t)(uintptr_t)c->hd.p, (uint64_t)(uintptr_t)c->partial.p,
@@ -828,7 +905,7 @@ int hot_destroy(hot_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   for (DevBuf* b : {&c->coef, &c->st, &c->hd, &c->partial, &c->stats, &c->flag, &c->amat, &c->efield, &c->acc,
-                    &c->probe, &c->abl})
+                    &c->probe, &c->abl, &c->hist})
     if (b->p) (void)hipFree(b->p);
   for (auto& s : c->ring) {
     if (s.pending && s.ev) (void)hipEventSynchronize(s.ev);
@@ -963,7 +1040,7 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     c->na_pending = false;
   }
   Plan P;
-  if ((rc = prepare_into(c, slm, 1, &M, xyz, theta0, theta0 == nullptr, seed, P, (TrapCoef*)(c->na_host + L.coef),
+  if ((rc = prepare_into(c, HOT_ONTHEFLY, slm, 1, &M, xyz, theta0, theta0 == nullptr, seed, P, (TrapCoef*)(c->na_host + L.coef),
                          (TrapState*)(c->na_host + L.st), (HoloDesc*)(c->na_host + L.hd))))
     return rc;
   char* base = (char*)c->scratch;
@@ -981,36 +1058,72 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   HIP_TRY(launch_fill_u32(c->stream, (unsigned*)acc_of(1), 0u, 2 * kAccRegions * M));
   HIP_TRY(launch_fill_u32(c->stream, (unsigned*)flag, 0u, 1));
   if (w0) HIP_TRY(launch_import_w(c->stream, w0, st[0], M));
-  IterArgs a;
-  a.fg = P.fg;
-  a.B = 1;
-  a.nt = P.nt;
-  a.q = P.q;
-  a.tpl = P.tpl;
-  a.rows = P.rows;
-  a.mmax = P.mmax;
-  a.one = P.one;
-  a.fract = P.fract;
-  a.coef = (const TrapCoef*)(base + L.coef);
-  a.hd = (const HoloDesc*)(base + L.hd);
-  a.T = M;
-  a.acc_scale = P.acc_scale;
-  a.acc_unscale = P.acc_unscale;
-  a.stats = dstats;
-  a.stat_stride = K + 1;
-  a.flag = flag;
-  for (int k = 0; k <= K; ++k) {
-    a.upd = k == 0 ? 0 : kGSW;
-    a.st_in = k == 0 ? st[0] : st[(k - 1) & 1];
-    a.st_out = st[k & 1];
-    a.acc_in = acc_of(k % 3);
-    a.acc_out = acc_of((k + 1) % 3);
-    a.acc_zero = acc_of((k + 2) % 3);
-    a.kstat = k - 1;
-    a.phase = k == K ? phase : nullptr;
-    HIP_TRY(launch_iter(c->stream, a));
+  const HoloDesc* hd = (const HoloDesc*)(base + L.hd);
+  if (P.tiles) {
+    SepArgs a;
+    a.shape = P.tile;
+    a.sc = P.tile_mc;
+    a.B = 1;
+    a.nx = P.nx;
+    a.ny = P.ny;
+    a.mmax = P.mmax;
+    a.one_m = P.one.m;
+    a.one_off = P.one.off;
+    a.coef = (const TrapCoef*)(base + L.coef);
+    a.hd = hd;
+    a.flag = flag;
+    a.T = M;
+    a.acc_scale = P.acc_scale;
+    a.acc_unscale = P.acc_unscale;
+    // V of the last masks, for their figures of merit: a ring behind the workspace
+    float2* hist = (float2*)(base + kScratchBytes);
+    const int ring = std::max(1, std::min({K, kHistMasks, (int)(kScratchHistBytes / (sizeof(float2) * (size_t)M))}));
+    for (int k = 0; k <= K; ++k) {
+      a.upd = k == 0 ? 0 : kGSW;
+      a.st_in = k == 0 ? st[0] : st[(k - 1) & 1];
+      a.st_out = st[k & 1];
+      a.acc_in = acc_of(k % 3);
+      a.acc_out = acc_of((k + 1) % 3);
+      a.acc_zero = acc_of((k + 2) % 3);
+      a.phase = k == K ? phase : nullptr;
+      const int slot = k > 0 ? (k - 1) % ring : 0;
+      a.hist = stats && k > 0 ? hist + (size_t)slot * M : nullptr;
+      HIP_TRY(launch_tile(c->stream, a));
+      if (stats && k > 0 && (slot == ring - 1 || k == K))
+        HIP_TRY(launch_stats(c->stream, slot + 1, 1, M, hist, hd, st[0], dstats, k - 1 - slot, K + 1));
+    }
+  } else {
+    IterArgs a;
+    a.fg = P.fg;
+    a.B = 1;
+    a.nt = P.nt;
+    a.q = P.q;
+    a.tpl = P.tpl;
+    a.rows = P.rows;
+    a.mmax = P.mmax;
+    a.one = P.one;
+    a.fract = P.fract;
+    a.coef = (const TrapCoef*)(base + L.coef);
+    a.hd = (const HoloDesc*)(base + L.hd);
+    a.T = M;
+    a.acc_scale = P.acc_scale;
+    a.acc_unscale = P.acc_unscale;
+    a.stats = dstats;
+    a.stat_stride = K + 1;
+    a.flag = flag;
+    for (int k = 0; k <= K; ++k) {
+      a.upd = k == 0 ? 0 : kGSW;
+      a.st_in = k == 0 ? st[0] : st[(k - 1) & 1];
+      a.st_out = st[k & 1];
+      a.acc_in = acc_of(k % 3);
+      a.acc_out = acc_of((k + 1) % 3);
+      a.acc_zero = acc_of((k + 2) % 3);
+      a.kstat = k - 1;
+      a.phase = k == K ? phase : nullptr;
+      HIP_TRY(launch_iter(c->stream, a));
+    }
   }
-  HIP_TRY(launch_finish(c->stream, 1, M, acc_of((K + 1) % 3), P.acc_unscale, a.hd, st[K & 1], V, dstats, K, K + 1));
+  HIP_TRY(launch_finish(c->stream, 1, M, acc_of((K + 1) % 3), P.acc_unscale, hd, st[K & 1], V, dstats, K, K + 1));
   if (w_out || theta_out) HIP_TRY(launch_export_state(c->stream, st[K & 1], M, w_out, theta_out));
   if (stats) {
     // statistics and flag through the pinned staging buffer (its own regions, not the tables')
@@ -1039,6 +1152,9 @@ int hot_gsw_batched(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M,
                c->variant == HOT_SEPARABLE ? HOT_SEPARABLE : HOT_ONTHEFLY);
 }
 
+// The variant that Eq. 1 and its adjoint run on (the stored variant has no kernels of its own for them).
+static int fa_variant(const hot_ctx* c) { return c->variant == HOT_SEPARABLE ? HOT_SEPARABLE : HOT_ONTHEFLY; }
+
 int hot_forward_V(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M, const double* xyz,
                   const float* phase, float* V) {
   if (!c) return fail(HOT_EINVAL, "ctx is NULL");
@@ -1049,8 +1165,16 @@ int hot_forward_V(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M, c
   if ((rc = set_dev(c))) return rc;
   Plan P;
   std::vector<double> zeros(T, 0.0);
-  if ((rc = prepare(c, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
+  if ((rc = prepare(c, fa_variant(c), slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, M, false))) return rc;
+  if (P.tiles) {
+    if ((rc = ensure(c, c->partial, sizeof(float2) * (size_t)P.T * P.nblk_tile))) return rc;
+    SepArgs a = tile_args(c, P, 1, const_cast<float*>(phase), 0);
+    HIP_TRY(launch_tile(c->stream, a));
+    HIP_TRY(launch_reduce(c->stream, B, P.mmax, P.nblk_tile, a.inv_n, (const float2*)c->partial.p,
+                          (const HoloDesc*)c->hd.p, V));
+    return HOT_OK;
+  }
   if (c->variant == HOT_SEPARABLE) {
     if ((rc = ensure(c, c->partial, sizeof(float2) * (size_t)P.T * P.nblk_sep))) return rc;
     SepArgs a = sep_args(c, P, 1, const_cast<float*>(phase), 0);
@@ -1078,8 +1202,15 @@ int hot_adjoint(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M, con
   if ((rc = set_dev(c))) return rc;
   Plan P;
   std::vector<double> zeros(T, 0.0);
-  if ((rc = prepare(c, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
+  if ((rc = prepare(c, fa_variant(c), slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, M, false))) return rc;
+  if (P.tiles) {
+    SepArgs a = tile_args(c, P, 3, const_cast<float*>(phase), 0);
+    a.vin = G;
+    a.grad = grad_phase;
+    HIP_TRY(launch_tile(c->stream, a));
+    return HOT_OK;
+  }
   if (c->variant == HOT_SEPARABLE) {
     SepArgs a = sep_args(c, P, 3, const_cast<float*>(phase), 0);
     a.vin = G;
@@ -1112,10 +1243,11 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   if (reps < 1) return fail(HOT_EINVAL, "reps = %d < 1", reps);
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
+  if ((rc = prepare(c, c->variant, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
   const bool stored = c->variant == HOT_STORED;
   const bool separable = c->variant == HOT_SEPARABLE;
-  const int nblk = stored ? P.nblk_stored : separable ? P.nblk_sep : std::max(P.fg.nblk(), P.fgf.nblk());
+  const bool tiles = P.tiles;
+  const int nblk = stored ? P.nblk_stored : tiles ? P.nblk_tile : separable ? P.nblk_sep : std::max(P.fg.nblk(), P.fgf.nblk());
   if ((rc = upload_tables(c, slm, P, xyz, &M))) return rc;
   if ((rc = ensure(c, c->partial, sizeof(float2) * (size_t)P.T * nblk))) return rc;
   if ((rc = ensure(c, c->stats, sizeof(float) * 3 * 2))) return rc;
@@ -1134,7 +1266,7 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   a.upd = 2;
   a.st_in = st[0];
   a.st_out = st[1];
-  SepArgs sa = sep_args(c, P, 0, phase, 1);
+  SepArgs sa = tiles ? tile_args(c, P, 0, phase, 1) : sep_args(c, P, 0, phase, 1);
   sa.upd = 2;
   sa.st_in = st[0];
   sa.st_out = st[1];
@@ -1147,10 +1279,10 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     SepArgs x = sa;
     x.mode = mode;
     if (mode == 0) x.phase = nullptr;  // as in every iteration but the last
-    return launch_sep(c->stream, x);
+    return tiles ? launch_tile(c->stream, x) : launch_sep(c->stream, x);
   };
   auto g0 = [&]() -> hipError_t {
-    if (separable) return sep_mode(0);
+    if (separable || tiles) return sep_mode(0);
     if (!stored) return launch_iter(c->stream, a);
     hipError_t e = launch_backward_stored(c->stream, P.n, 1, (const float2*)c->amat.p, st[0], hd, phase,
                                           (float2*)c->efield.p);
@@ -1169,14 +1301,14 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     if (stored) return hipSuccess;
     hipError_t e = launch_fill_u32(c->stream, (unsigned*)acc_buf(c, P, 0), 0u, 2 * kAccRegions * P.T);
     if (e != hipSuccess) return e;
-    if (separable) {
+    if (separable || tiles) {
       SepArgs p0 = sa;
       p0.upd = 0;
       p0.phase = nullptr;
       p0.acc_in = acc_buf(c, P, 2);
       p0.acc_out = acc_buf(c, P, 0);
       p0.acc_zero = acc_buf(c, P, 1);
-      return launch_sep(c->stream, p0);
+      return tiles ? launch_tile(c->stream, p0) : launch_sep(c->stream, p0);
     }
     IterArgs p0 = a;
     p0.upd = 0;
@@ -1186,13 +1318,13 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     return launch_iter(c->stream, p0);
   };
   auto g2 = [&]() {
-    if (separable) return sep_mode(2);
+    if (separable || tiles) return sep_mode(2);
     return stored ? launch_backward_stored(c->stream, P.n, 1, (const float2*)c->amat.p, st[0], hd, phase,
                                            (float2*)c->efield.p)
                   : launch_backward(c->stream, P.nx, P.ny, 1, P.fract, 1, coef, st[0], hd, phase, 0, nullptr, nullptr);
   };
   auto g3 = [&]() {
-    if (separable) return sep_mode(1);
+    if (separable || tiles) return sep_mode(1);
     return stored ? launch_forward_stored(c->stream, P.n, 1, P.mmax, (const float2*)c->amat.p,
                                           (const float2*)c->efield.p, hd, part)
                   : launch_forward(c->stream, P.fgf, 1, P.mmax, P.tplf, P.fract, coef, hd + 1, phase, part);
@@ -1203,8 +1335,8 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   do {
     // V (and the direct path's buffer 0) must hold a real trap field before an update reads it
     if (g2() != hipSuccess || g3() != hipSuccess ||
-        launch_reduce(c->stream, 1, P.mmax, stored ? P.nblk_stored : separable ? P.nblk_sep : P.fgf.nblk(), inv_n,
-                      part, stored || separable ? hd : hd + 1, V) != hipSuccess ||
+        launch_reduce(c->stream, 1, P.mmax, stored ? P.nblk_stored : tiles ? P.nblk_tile : separable ? P.nblk_sep : P.fgf.nblk(), inv_n,
+                      part, stored || separable || tiles ? hd : hd + 1, V) != hipSuccess ||
         prime() != hipSuccess || g0() != hipSuccess || g1() != hipSuccess) {
       out = fail(HOT_EDEVICE, "launch failed");
       break;
@@ -1245,7 +1377,7 @@ int hot_pixel_pass_variant(hot_ctx* c, const hot_slm* slm, int32_t M, const doub
   if (reps < 1) return fail(HOT_EINVAL, "reps = %d < 1", reps);
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
+  if ((rc = prepare(c, HOT_ONTHEFLY, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, &M))) return rc;
   const int nb = abl_blocks(mapping, block, slm->nx, slm->ny);
   if ((rc = ensure(c, c->abl, sizeof(float4) * (size_t)nb * M))) return rc;

@@ -162,12 +162,14 @@ hipError_t launch_forward_stored(hipStream_t s, int n, int B, int mmax, const fl
 // Separable reformulation on the matrix cores (any batch); the per-block tables of Eq. 2's two
 // factors are computed in LDS from coef.
 struct SepArgs {
+  int shape = 0;  // tile kernels: index into kTileShapes
   int mode = 0;  // 0 iteration, 1 trap pass from `phase`, 2 pixel pass, 3 adjoint (G in vin, grad out)
   int W = 4;     // tiles per block: a block covers 16 rows x 16 W columns
   int kh = 1;    // mode 0: waves per tile (1, or 2 taking half of the traps each)
   int B = 1, nx = 0, ny = 0, mmax = 0;
   int one_m = 0, one_off = 0;  // B == 1: the hologram's trap count and offset, passed by value
   int sc = 16;   // traps per LDS super-chunk (multiple of 16); sep_lds_bytes(W, sc, mmax, kh) <= kSepLdsMax
+                 // (tile kernels: tile_lds_bytes(shape, sc, mmax) <= kLdsMax)
   const TrapCoef* coef = nullptr;
   const HoloDesc* hd = nullptr;
   const TrapState* st_in = nullptr;
@@ -182,6 +184,7 @@ struct SepArgs {
   float* stats = nullptr;
   int kstat = 0, stat_stride = 1;
   int upd = 0;  // mode 0: 0 none, 1 GS, 2 GSW
+  float2* hist = nullptr;  // tile kernels, mode 0: V of the previous mask is written here when not null
   int* flag = nullptr;
   float inv_n = 0.0f;
   float* phase = nullptr;  // mode 0: written when non-null; modes 1, 3: read; mode 2: written
@@ -200,6 +203,34 @@ inline size_t sep_lds_bytes(int W, int sc, int mmax, int kh = 1) {
   const size_t mp = (size_t)(mmax + 15) / 16 * 16;
   return 40 * mp + 8 * (size_t)(sc + 2) * (16 * W + 32) + 8 * (size_t)W * kh * sc + (kh == 2 ? 2048 * (size_t)W * kh : 0);
 }
+
+// Tile kernels (hot_tiles.hip): both passes as complex contractions on the FP16 matrix cores at FP32
+// accuracy, any batch, the same modes and arguments as the separable kernels (W and kh unused).  A
+// block covers 16 rt rows x 16 cw ctw columns; rt cw groups of kh waves, each with a 16 x 16 ctw part
+// of it, the waves of a group sharing the traps.
+struct TileShape {
+  int rt, cw, ctw, kh;
+  constexpr int waves() const { return rt * cw * kh; }
+  constexpr int rows() const { return 16 * rt; }
+  constexpr int cols() const { return 16 * cw * ctw; }
+  constexpr int gx(int nx) const { return (nx + cols() - 1) / cols(); }
+  constexpr int gy(int ny) const { return (ny + rows() - 1) / rows(); }
+};
+enum { kTile32 = 0, kTile32Split = 1, kTile64 = 2 };
+constexpr TileShape kTileShapes[] = {{2, 2, 1, 1}, {2, 2, 1, 2}, {4, 2, 2, 1}};
+constexpr int kTileFragWords = 528;  // words of a 16 x 16 table fragment
+// dynamic LDS for super-chunks of mc traps (a multiple of 16): fragments of the column table, of the
+// weighted row table (both split) and of the row table (FP32), group constants, trap sums, the
+// weights of all traps, per-wave words, and with kh > 1 the waves' partial pixel sums
+inline size_t tile_lds_bytes(const TileShape& t, int mc, int mmax) {
+  const size_t mp = (size_t)(mmax + 15) / 16 * 16, ct = t.cw * t.ctw, rt = t.rt;
+  return (size_t)(mc / 16) * (4 * kTileFragWords * (ct + rt) + 2048 * rt) + (size_t)mc * (16 * (ct + rt) + 8 * t.rt * t.cw) +
+         8 * mp + 8 * (size_t)t.waves() + (t.kh > 1 ? 2048 * (size_t)t.waves() * t.ctw : 0);
+}
+hipError_t launch_tile(hipStream_t s, const SepArgs& a);
+// Figures of merit of n consecutive masks from their V (hist [n][T]) into stats[b][k0 ..].
+hipError_t launch_stats(hipStream_t s, int n, int B, int T, const float2* hist, const HoloDesc* hd,
+                        const TrapState* st, float* stats, int k0, int stat_stride);
 
 // Micro-benchmarks (hot_probes.hip): issue-rate probe of kind 0 (FMA), 1 (sin/cos) or 2 (the
 // direct passes' term: 4 FMA + sin + cos); every wave writes {shader clock, shader clock,
@@ -224,6 +255,7 @@ hipError_t launch_encode_u8(hipStream_t s, const float* phase, uint8_t* frame, i
 // The fixed device workspace of the allocation-free entry point (hot_scratch.hip): its size, and
 // its device address on `device` (which must be the current device).
 constexpr size_t kScratchBytes = size_t(1) << 20;
+constexpr size_t kScratchHistBytes = size_t(1) << 20;  // behind it: V of the last masks (tile kernels)
 hipError_t scratch_address(int device, void** out);
 
 // Small helpers.

@@ -1,0 +1,614 @@
+// hot_tiles.hip -- both passes as complex contractions on the FP16 matrix cores, at FP32 accuracy.
+//
+// Eq. 2 separates per trap: Delta_rev = (g U^2 + a U) + (g V^2 + b V), so
+//   e^{i 2pi Delta_j^m} = X_m(c) Y_m(r),  X_m(c) = e^{i 2pi (g U_c^2 + a U_c)},  Y_m(r) = e^{i 2pi (g V_r^2 + b V_r)},
+// and with the trap weights c_m = w_m e^{i theta_m}
+//   pixel pass (Eq. 3)  S[r][c] = sum_m (c_m Y_m(r)) X_m(c),          phi = arg S
+//   trap pass (Eq. 1)   T[r][m] = sum_c e^{i phi[r][c]} conj X_m(c),  V_m = (1/N) sum_r conj Y_m(r) T[r][m].
+// The direct sums (k_iter, k_backward, k_forward) pay one sine and cosine per (pixel, trap) and pass; here
+// a block computes 16 (rows + columns) of them per 16 traps for its tile of pixels, and the (pixel, trap)
+// work is matrix products.
+//
+// Precision.  v_mfma_f32_16x16x32_f16 multiplies halves exactly and accumulates in FP32 at 16 times the
+// rate of the FP32 products (16 cycles for 16 x 16 x 32 against 32 for 16 x 16 x 4).  Every real factor v
+// (|v| <= 1) is carried as hi = f16(v), lo = f16(v - hi), which leaves |v - hi - lo| <= 2^-24, the
+// rounding of an FP32 value just below 1, and a product is hi hi + hi lo + lo hi (the dropped lo lo is
+// below 2^-24): three half products for one FP32 product.  Measured against 64 bits over grids of 48 to
+// 2048 pixels a side and 3 to 1000 traps, fields and gradients are as close as with FP32 matrix products
+// (3.1e-7 against 3.3e-7 relative for the adjoint of 8 x 512^2 x 64) and closer than the direct sums
+// (7.2e-7), whose per-term arguments reach several revolutions.  The weights are scaled by a power of two
+// so that the largest is below 1; all the rest (arguments, sine and cosine, normalisation, trap sums) is
+// FP32 or FP64 as in the other kernels.
+//
+// MFMA 16x16x32 operands: lane l = i + 16 g holds A[i][8 g ..+7] and B[8 g ..+7][i]; result D[i][j] is in
+// lane j + 16 (i / 4), register i % 4.  Eight halves are four complex entries (re, im), so a product
+// covers 16 traps (pixel pass) or 16 columns (trap pass):
+//   pixel pass  Re S = (xr, xi) . (wr, -wi), Im S = (xr, xi) . (wi, wr): the second operand is the first
+//               with its halves turned, in registers.  Columns are i, rows j, so a lane ends with four
+//               consecutive pixels of one row.
+//   epilogue    E = S / |S|, and the phase where it is wanted (a solve's last mask)
+//   trap pass   Re T = (Er, Ei) . (xr, xi), Im T = (Ei, -Er) . (xr, xi), the lane's four E values being
+//               its eight halves of the operand; T is folded over its 16 rows with conj Y in FP32 and the
+//               lane groups are summed.
+//
+// What bounds it.  One iteration of 1024^2 x 256 is 8.6 GFLOP of products (5.1 us at the rate of the
+// halves) and 24.8 us per launch, against 110 us of the direct sums; 512^2 x 100 takes 7.5 us (15.9).
+// On the larger grid the rest is building the tables (twice per block: traps go through the LDS in
+// super-chunks), on the smaller latency: 1.1 us from one launch to the next, 1.2 us until the first
+// coefficients are there, 1.2 us for the last trap sums to be added, and between them phases of a few
+// hundred instructions per wave at one or two waves per SIMD.
+#include "hot_device.h"
+
+#include <algorithm>
+
+namespace hot {
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4 mfma32(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a), __builtin_bit_cast(half8v, b), c, 0, 0, 0);
+}
+
+// x + i y as two packed pairs of halves: hi = f16(x), f16(y), and lo = f16 of what hi leaves, each in
+// one rounding from the very bits of hi (|x - hi - lo| <= 2^-24 for |x| <= 1).
+struct Split {
+  unsigned hi, lo;
+};
+__device__ __forceinline__ Split split(float x, float y) {
+  const half2v h = {(_Float16)x, (_Float16)y};
+  Split s;
+  s.hi = __builtin_bit_cast(unsigned, h);
+  asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %0, %1, -1.0, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
+      : "=&v"(s.lo)
+      : "v"(s.hi), "v"(x), "v"(y));
+  return s;
+}
+// ... of x - i y
+__device__ __forceinline__ Split split_conj(float x, float y) {
+  const half2v h = {(_Float16)x, (_Float16)(-y)};
+  Split s;
+  s.hi = __builtin_bit_cast(unsigned, h);
+  asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %0, %1, -1.0, -%3 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
+      : "=&v"(s.lo)
+      : "v"(s.hi), "v"(x), "v"(y));
+  return s;
+}
+// (a, b) -> (-b, a) and (a, b) -> (b, -a), halves of a word (exact)
+__device__ __forceinline__ unsigned turn_p(unsigned v) {
+  unsigned r;
+  asm("v_pk_mul_f16 %0, %1, 1.0 op_sel:[1,0] op_sel_hi:[0,0] neg_lo:[1,0]" : "=v"(r) : "v"(v));
+  return r;
+}
+__device__ __forceinline__ unsigned turn_m(unsigned v) {
+  unsigned r;
+  asm("v_pk_mul_f16 %0, %1, 1.0 op_sel:[1,0] op_sel_hi:[0,0] neg_hi:[1,0]" : "=v"(r) : "v"(v));
+  return r;
+}
+
+// Two tiles' partial sums (re, im) of the four lane groups, summed over the groups: lane group 0
+// gets tile a's re, group 1 tile b's re, group 2 tile a's im, group 3 tile b's im.  Each sum is
+// (p0 + p2) + (p1 + p3) of the groups' partials.
+__device__ __forceinline__ float2 swap32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned x = r[0], y = r[1];  // (a bit_cast of the vector's element itself would read element 0)
+  return make_float2(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y));
+}
+__device__ __forceinline__ float2 swap16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned x = r[0], y = r[1];  // (a bit_cast of the vector's element itself would read element 0)
+  return make_float2(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y));
+}
+__device__ __forceinline__ float sum_groups(float2 a, float2 b) {
+  const float2 p = swap32(a.x, a.y), q = swap32(b.x, b.y);
+  const float2 r = swap16(p.x + p.y, q.x + q.y);
+  return r.x + r.y;
+}
+
+// A fragment of a table: 16 rows or columns x 16 traps of complex entries, each a word of two halves
+// (re, im).  Entry (i, t) of the hi part is word 4 i + 132 (t / 4) + t % 4, of the lo part 64 words
+// further: a lane's four consecutive traps are one 16-byte read (matrix operand with the traps as
+// k), a lane's four consecutive i of one trap are four words 4 apart (matrix operand with i as k),
+// and with 132 words per group of four traps both kinds of access reach every bank evenly.
+constexpr int kFragWords = kTileFragWords;
+constexpr int kTqWords = 132, kLoWords = 64;
+
+// MODE 0: one iteration: GS/GSW update (upd 1 / 2, recomputed by every block from the previous mask's
+//   fixed-point sums acc_in; 0: st_in as is), pixel pass, trap pass; the phase is written when not null.
+//   Each trap's block sum is added to acc_out's region of the wave's XCD, block (0, 0, b) writes
+//   hologram b's new state and clears its part of acc_zero, as in k_iter.  The figures of merit are not
+//   taken here: that block leaves V in `hist` (when not null) and k_stats works on several masks at a
+//   time (computed by one block before its pixel pass they held back the whole launch: 512^2 x 100 9.5
+//   against 8.7 us).
+// MODE 1: trap pass alone from the given phase (Eq. 1): per-block partials
+// MODE 2: pixel pass alone from the given state (phase out)
+// MODE 3: adjoint of Eq. 1: weights G_m (vin), grad[j] = (1/N) Im(e^{-i phi_j} S_j) for the given phase
+//
+// Grid (ceil(nx / 16 CW CTW), ceil(ny / 16 RT), B), RT CW KH waves: wave (rt, cwv, part) has row tile
+// rt, column tiles CTW cwv .. + CTW - 1 and share `part` of the trap tiles of each super-chunk (mc traps);
+// the KH partial pixel sums of a tile meet in LDS and are added in a fixed order.  The waves build the
+// tables together: a wave always has the same column tile tx and row tile ty, whose group constants
+// (the phase about the tile's centre column or row, formed in FP64 and rounded once; K, slope, curvature)
+// it forms for itself, so no barrier stands between them and the entries.  Columns past nx and rows past
+// ny get the formula's values and pixels with E = 0; traps past M repeat trap M - 1 with weight 0.
+// Dynamic LDS: tile_lds_bytes.
+template <int RT, int CW, int CTW, int KH, int MODE>
+__global__ void __launch_bounds__(RT * CW * KH * 64, RT * CW * KH >= 16 ? 4 : 2)
+k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
+       const unsigned long long* __restrict__ acc_in, int one_m, int one_off, int T, float unscale, int nx, int ny,
+       int mc, int upd, const HoloDesc* __restrict__ hd, TrapState* __restrict__ st_out,
+       const float* __restrict__ vin, float2* __restrict__ hist, int* __restrict__ flag, float inv_n,
+       float* __restrict__ phase, float* __restrict__ grad, float2* __restrict__ partial,
+       unsigned long long* __restrict__ acc_out, unsigned long long* __restrict__ acc_zero, float scale) {
+  constexpr int NS = RT * CW, NW = NS * KH, NT = NW * 64, CT = CW * CTW;
+  constexpr int XS = NW / CT, YS = NW / RT;  // waves sharing a column tile's (row tile's) table
+  static_assert(NW % CT == 0 && NW % RT == 0, "whole waves per column and row tile");
+  constexpr bool kPixel = MODE != 1, kTrap = MODE <= 1;
+  extern __shared__ float4 lds4[];
+  const int b = blockIdx.z;
+  int M = one_m, off = one_off;
+  if (one_m <= 0) {
+    M = hd[b].m;
+    off = hd[b].off;
+  }
+  const int Mp = (M + 15) & ~15;
+  const int ntm = mc >> 4;
+  unsigned* xf = reinterpret_cast<unsigned*>(lds4);              // [CT][ntm] X fragments
+  unsigned* wf = xf + CT * ntm * kFragWords;                     // [RT][ntm] weighted Y fragments
+  float4* yf = reinterpret_cast<float4*>(wf + RT * ntm * kFragWords);  // [RT][ntm][2][64] Y, FP32
+  float4* refs = yf + RT * ntm * 128;                            // group constants {K, s, q}: [CT + RT][mc]
+  float4* sx = refs + (CT + RT) * mc;                            // KH > 1: [NW][CTW][2][64] partial pixel sums
+  float2* red = reinterpret_cast<float2*>(sx + (KH > 1 ? NW * CTW * 128 : 0));  // [NS][mc] trap sums
+  float2* cw = red + NS * mc;                                    // [Mp] c_m
+  float* sh = reinterpret_cast<float*>(cw + Mp);                 // [2 NW]
+
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+  const int tw = wave % NS, part = wave / NS;    // the wave's pixels, and its share of the traps
+  const int rt = tw / CW, cwv = tw - rt * CW;    // its row tile, and its group of column tiles
+  const int row0 = blockIdx.y * (16 * RT), cb = blockIdx.x * (16 * CT);
+  const int r = row0 + 16 * rt + li;
+  const int c0 = cb + 16 * CTW * cwv + 4 * g;  // the lane's first column of its first tile
+  const size_t pix0 = (size_t)b * nx * ny + (size_t)r * nx + c0;
+
+  const int ewofs = 16 * g + kTqWords * (li >> 2) + (li & 3);  // entry (4 g + v, trap li): + 4 v
+  const int pofs = 4 * li + kTqWords * g;                      // entries (li, traps 4 g .. 4 g + 3)
+  float fi[4], fq[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    fi[v] = (float)(4 * g + v - 8);
+    fq[v] = fi[v] * fi[v];
+  }
+
+  // group constants of this wave's share of the tables, traps [k0, k0 + n): tile tx for the trap
+  // tiles wave / CT, + XS, ..., and row tile ty for wave / RT, + YS, ...; written and read by this
+  // wave alone
+  const int tx = wave % CT, ty = wave % RT, jx = wave / CT, jy = wave / RT;
+  float4* rx = refs + tx * mc;
+  float4* ry = refs + (CT + ty) * mc;
+  auto group = [&](const TrapCoef& k, double lin, double X) {
+    const double kk = __builtin_fma(k.g, X * X, lin * X);
+    double sl = __builtin_fma(4.0 * k.g, X, 2.0 * lin);
+    sl -= __builtin_rint(sl);
+    double q = 4.0 * k.g;
+    q -= __builtin_rint(q);
+    return make_float4((float)(kk - __builtin_floor(kk)), (float)sl, (float)q, 0.0f);
+  };
+  const double Xc = (double)(2 * (cb + 16 * tx + 8) - (nx - 1)), Yc = (double)(2 * (row0 + 16 * ty + 8) - (ny - 1));
+  auto stage_refs = [&](int k0, int n) {
+    for (int j = g; 16 * (jx + XS * j) < n; j += 4) {
+      const int m = 16 * (jx + XS * j) + li;
+      rx[m] = group(coef[off + min(k0 + m, M - 1)], coef[off + min(k0 + m, M - 1)].a, Xc);
+    }
+    for (int j = g; 16 * (jy + YS * j) < n; j += 4) {
+      const int m = 16 * (jy + YS * j) + li;
+      ry[m] = group(coef[off + min(k0 + m, M - 1)], coef[off + min(k0 + m, M - 1)].b, Yc);
+    }
+  };
+  auto entries = [&](const float4* ks, int tt, float2 (&e)[4]) {
+    const float4 k = ks[16 * tt + li];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float t = __builtin_fmaf(k.z, fq[v], __builtin_fmaf(k.y, fi[v], k.x));
+      e[v] = make_float2(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+    }
+  };
+  auto put_x = [&](int tt) {
+    float2 e[4];
+    entries(rx, tt, e);
+    unsigned* x = xf + (tx * ntm + tt) * kFragWords + ewofs;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const Split s = split(e[v].x, e[v].y);
+      x[4 * v] = s.hi;
+      x[4 * v + kLoWords] = s.lo;
+    }
+  };
+  int wexp = 0;
+  auto put_w = [&](int tt, int k0, const float2 (&e)[4]) {
+    const float2 c = cw[k0 + 16 * tt + li];
+    const float cx = __builtin_amdgcn_ldexpf(c.x, -wexp), cy = __builtin_amdgcn_ldexpf(c.y, -wexp);
+    unsigned* w = wf + (ty * ntm + tt) * kFragWords + ewofs;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const Split s = split_conj(__builtin_fmaf(cx, e[v].x, -cy * e[v].y), __builtin_fmaf(cx, e[v].y, cy * e[v].x));
+      w[4 * v] = s.hi;
+      w[4 * v + kLoWords] = s.lo;
+    }
+  };
+  auto put_y = [&](int tt, const float2 (&e)[4]) {
+    float4* y = yf + (ty * ntm + tt) * 128 + lane;
+    y[0] = make_float4(e[0].x, e[0].y, e[1].x, e[1].y);
+    y[64] = make_float4(e[2].x, e[2].y, e[3].x, e[3].y);
+  };
+  auto get_y = [&](int f, float2 (&e)[4]) {
+    const float4 y0 = yf[f * 128 + lane], y1 = yf[f * 128 + 64 + lane];
+    e[0] = make_float2(y0.x, y0.y);
+    e[1] = make_float2(y0.z, y0.w);
+    e[2] = make_float2(y1.x, y1.y);
+    e[3] = make_float2(y1.z, y1.w);
+  };
+  auto rebuild = [&](int k0, int n, bool weighted) {
+    const int nt = n >> 4;
+    __syncthreads();  // the previous super-chunk is no longer read
+    stage_refs(k0, n);
+    for (int tt = jx; tt < nt; tt += XS) put_x(tt);
+    for (int tt = jy; tt < nt; tt += YS) {
+      float2 e[4];
+      entries(ry, tt, e);
+      put_y(tt, e);
+      if (weighted) put_w(tt, k0, e);
+    }
+    __syncthreads();
+  };
+
+  const int nsc = (Mp + mc - 1) / mc;
+  const int n0 = min(mc, Mp), nt0 = n0 >> 4;
+  const VAcc vacc{acc_in, T, off, unscale};
+  const bool lead = blockIdx.x == 0 && blockIdx.y == 0;
+  const bool holds = wave * 64 < M;  // the wave holds traps
+  const int tm = min((int)threadIdx.x, M - 1);
+  TrapState s_first = {0.0f, 0.0f, 0.0f, 0.0f};
+  unsigned long long w_first[kAccRegions] = {};
+  stage_refs(0, n0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (kPixel && MODE != 3 && holds) {
+    s_first = st_in[off + tm];
+    if (MODE == 0) vacc.load(tm, w_first);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  for (int tt = jx; tt < nt0; tt += XS) put_x(tt);
+  constexpr int YK = 4;  // this wave's first row fragments stay in registers until the weights are known
+  float2 ey[YK][4];
+#pragma unroll
+  for (int j = 0; j < YK; ++j) {
+    const int tt = jy + YS * j;
+    if (tt < nt0) {
+      entries(ry, tt, ey[j]);
+      put_y(tt, ey[j]);
+    }
+  }
+  for (int tt = jy + YS * YK; tt < nt0; tt += YS) {
+    float2 e[4];
+    entries(ry, tt, e);
+    put_y(tt, e);
+  }
+
+  u32x4 eh[CTW], el[CTW], fh[CTW], fl[CTW];  // E = (Er, Ei) hi, lo and (Ei, -Er) hi, lo
+  auto put_e = [&](int ct, const float* er, const float* ei) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const Split s = split(er[v], ei[v]);
+      eh[ct][v] = s.hi;
+      el[ct][v] = s.lo;
+      fh[ct][v] = turn_m(s.hi);
+      fl[ct][v] = turn_m(s.lo);
+    }
+  };
+  auto inside = [&](int ct, int v) { return r < ny && c0 + 16 * ct + v < nx; };
+
+  if constexpr (kPixel) {
+    float wmax = 0.0f;
+    for (int m = M + (int)threadIdx.x; m < Mp; m += NT) cw[m] = make_float2(0.0f, 0.0f);
+    if (MODE == 3) {
+      for (int m = threadIdx.x; m < M; m += NT) {
+        const float2 gm = make_float2(vin[2 * (off + m)], vin[2 * (off + m) + 1]);
+        cw[m] = gm;
+        wmax = fmaxf(wmax, fmaxf(fabsf(gm.x), fabsf(gm.y)));
+      }
+    } else if (MODE == 2 || upd == 0) {
+      for (int m = threadIdx.x; m < M; m += NT) {
+        const TrapState s = m == (int)threadIdx.x ? s_first : st_in[off + m];
+        cw[m] = trap_weight(s);
+        wmax = fmaxf(wmax, fabsf(s.w));
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kAccRegions; ++q) asm volatile("" : "+v"(w_first[q]));  // (the sum stays here)
+      const float2 v_first = vacc.sum(w_first);
+      if (lead && hist != nullptr) {
+        if ((int)threadIdx.x < M) hist[off + threadIdx.x] = v_first;
+        for (int m = NT + (int)threadIdx.x; m < M; m += NT) hist[off + m] = vacc(m);
+      }
+      auto emit = [&](int m, const TrapState& st) {
+        if (lead) st_out[off + m] = st;
+        cw[m] = trap_weight(st);
+        wmax = fmaxf(wmax, fabsf(st.w));
+      };
+      update_traps<NT, VAcc, decltype(emit), true>(vacc, st_in, off, M, upd, sh, nullptr, lead ? flag : nullptr, emit,
+                                                   v_first, s_first);
+    }
+    wmax = wave_max(wmax);
+    if (lane == 0) sh[NW + wave] = wmax;
+    __syncthreads();
+    wmax = sh[NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) wmax = fmaxf(wmax, sh[NW + w]);
+    wexp = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(wmax));
+    // weighted Y of the first super-chunk
+#pragma unroll
+    for (int j = 0; j < YK; ++j) {
+      const int tt = jy + YS * j;
+      if (tt < nt0) put_w(tt, 0, ey[j]);
+    }
+    for (int tt = jy + YS * YK; tt < nt0; tt += YS) {
+      float2 e[4];
+      get_y(ty * ntm + tt, e);
+      put_w(tt, 0, e);
+    }
+    __syncthreads();
+    if (MODE == 0 && lead) {
+      for (int m = threadIdx.x; m < M; m += NT) {
+#pragma unroll
+        for (int q = 0; q < kAccRegions; ++q) acc_zero[(size_t)q * T + off + m] = 0ull;
+      }
+    }
+
+    f32x4 sre[CTW], sim[CTW];
+#pragma unroll
+    for (int ct = 0; ct < CTW; ++ct) {
+      sre[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      sim[ct] = sre[ct];
+    }
+    for (int s = 0; s < nsc; ++s) {
+      const int k0 = s * mc, n = min(mc, Mp - k0), nt = n >> 4;
+      if (s > 0) rebuild(k0, n, true);
+      const int th = (nt + KH - 1) / KH;
+      const int t0 = part * th, t1 = min(nt, t0 + th);
+#pragma unroll 2
+      for (int tt = t0; tt < t1; ++tt) {
+        const unsigned* wb = wf + (rt * ntm + tt) * kFragWords + pofs;
+        const u32x4 bh = *reinterpret_cast<const u32x4*>(wb), bl = *reinterpret_cast<const u32x4*>(wb + kLoWords);
+        u32x4 ch, cl;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          ch[v] = turn_p(bh[v]);
+          cl[v] = turn_p(bl[v]);
+        }
+#pragma unroll
+        for (int ct = 0; ct < CTW; ++ct) {
+          const unsigned* xb = xf + ((cwv * CTW + ct) * ntm + tt) * kFragWords + pofs;
+          const u32x4 ah = *reinterpret_cast<const u32x4*>(xb), al = *reinterpret_cast<const u32x4*>(xb + kLoWords);
+          sre[ct] = mfma32(ah, bh, sre[ct]);
+          sim[ct] = mfma32(ah, ch, sim[ct]);
+          sre[ct] = mfma32(ah, bl, sre[ct]);
+          sim[ct] = mfma32(ah, cl, sim[ct]);
+          sre[ct] = mfma32(al, bh, sre[ct]);
+          sim[ct] = mfma32(al, ch, sim[ct]);
+        }
+      }
+    }
+    if constexpr (KH > 1) {
+#pragma unroll
+      for (int ct = 0; ct < CTW; ++ct) {
+        float4* p = sx + (wave * CTW + ct) * 128 + lane;
+        p[0] = make_float4(sre[ct][0], sre[ct][1], sre[ct][2], sre[ct][3]);
+        p[64] = make_float4(sim[ct][0], sim[ct][1], sim[ct][2], sim[ct][3]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int ct = 0; ct < CTW; ++ct) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+          const float4* p = sx + ((tw + k * NS) * CTW + ct) * 128 + lane;
+          const float4 a = p[0], c = p[64];
+          const f32x4 ra = {a.x, a.y, a.z, a.w}, ia = {c.x, c.y, c.z, c.w};
+          sre[ct] = k == 0 ? ra : sre[ct] + ra;
+          sim[ct] = k == 0 ? ia : sim[ct] + ia;
+        }
+      }
+    }
+    if constexpr (MODE == 3) {
+#pragma unroll
+      for (int ct = 0; ct < CTW; ++ct) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if (inside(ct, v)) {
+            const size_t px = pix0 + 16 * ct + v;
+            const float pr = caller_phase_rev(phase[px]);
+            grad[px] = __builtin_amdgcn_ldexpf(
+                inv_n * (__builtin_amdgcn_cosf(pr) * sim[ct][v] - __builtin_amdgcn_sinf(pr) * sre[ct][v]), wexp);
+          }
+        }
+      }
+    } else {
+      if (phase != nullptr && part == 0) {  // (the last mask of a solve)
+#pragma unroll
+        for (int ct = 0; ct < CTW; ++ct) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (inside(ct, v)) phase[pix0 + 16 * ct + v] = phase_of(sim[ct][v], sre[ct][v]);
+        }
+      }
+      if constexpr (kTrap) {
+#pragma unroll
+        for (int ct = 0; ct < CTW; ++ct) {
+          float er[4], ei[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            // E = S / |S|, 1 where S = 0 (arg 0 = 0).  S is a sum of products of halves, multiples of
+            // 2^-48, over weights scaled to at most 1: |S|^2 neither underflows nor overflows.
+            const float x = sre[ct][v], y = sim[ct][v];
+            const float n2 = __builtin_fmaf(x, x, y * y);
+            const float inv = __builtin_amdgcn_rsqf(n2);
+            const bool in = inside(ct, v), zero = n2 == 0.0f;
+            er[v] = in ? (zero ? 1.0f : x * inv) : 0.0f;
+            ei[v] = in && !zero ? y * inv : 0.0f;
+          }
+          put_e(ct, er, ei);
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int ct = 0; ct < CTW; ++ct) {
+      float er[4], ei[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool in = inside(ct, v);
+        const float pr = in ? caller_phase_rev(phase[pix0 + 16 * ct + v]) : 0.0f;
+        er[v] = in ? __builtin_amdgcn_cosf(pr) : 0.0f;
+        ei[v] = in ? __builtin_amdgcn_sinf(pr) : 0.0f;
+      }
+      put_e(ct, er, ei);
+    }
+    __syncthreads();
+  }
+
+  if constexpr (kTrap) {
+    const int nblk = gridDim.x * gridDim.y, blk = blockIdx.y * gridDim.x + blockIdx.x;
+    // super-chunks: the one whose tables are in LDS first
+    for (int j = 0; j < nsc; ++j) {
+      const int s = kPixel ? nsc - 1 - j : j;
+      const int k0 = s * mc, n = min(mc, Mp - k0), nt = n >> 4;
+      if (j > 0) rebuild(k0, n, false);
+      const int th = (nt + KH - 1) / KH;
+      const int t0 = part * th, t1 = min(nt, t0 + th);
+      float* rw = reinterpret_cast<float*>(red) + 2 * (tw * mc + li) + (g >> 1);
+      for (int tt = t0; tt < t1; tt += 2) {  // two trap tiles at a time
+        f32x4 tre[2], tim[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int t = min(tt + p, t1 - 1);
+          tre[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+          tim[p] = tre[p];
+#pragma unroll
+          for (int ct = 0; ct < CTW; ++ct) {
+            const unsigned* xb = xf + ((cwv * CTW + ct) * ntm + t) * kFragWords + ewofs;
+            u32x4 xh, xl;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              xh[v] = xb[4 * v];
+              xl[v] = xb[4 * v + kLoWords];
+            }
+            tre[p] = mfma32(eh[ct], xh, tre[p]);
+            tim[p] = mfma32(fh[ct], xh, tim[p]);
+            tre[p] = mfma32(el[ct], xh, tre[p]);
+            tim[p] = mfma32(fl[ct], xh, tim[p]);
+            tre[p] = mfma32(eh[ct], xl, tre[p]);
+            tim[p] = mfma32(fh[ct], xl, tim[p]);
+          }
+        }
+        float2 q[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          float2 yv[4];
+          get_y(rt * ntm + min(tt + p, t1 - 1), yv);
+          float pr[2], pi[2];  // Re and Im of conj(y) t over rows (0, 1) and (2, 3)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const float2 a = yv[2 * h], c = yv[2 * h + 1];
+            const float tr0 = tre[p][2 * h], ti0 = tim[p][2 * h], tr1 = tre[p][2 * h + 1], ti1 = tim[p][2 * h + 1];
+            pr[h] = __builtin_fmaf(c.x, tr1, __builtin_fmaf(c.y, ti1, __builtin_fmaf(a.x, tr0, a.y * ti0)));
+            pi[h] = __builtin_fmaf(c.x, ti1, __builtin_fmaf(-c.y, tr1, __builtin_fmaf(a.x, ti0, -a.y * tr0)));
+          }
+          q[p] = make_float2(pr[0] + pr[1], pi[0] + pi[1]);
+        }
+        const float v = sum_groups(q[0], q[1]);
+        if (tt + (g & 1) < t1) rw[32 * (tt + (g & 1))] = v;
+      }
+      __syncthreads();
+      for (int m = threadIdx.x; m < n && k0 + m < M; m += NT) {
+        float2 acc = red[m];
+#pragma unroll
+        for (int w = 1; w < NS; ++w) {
+          acc.x += red[w * mc + m].x;
+          acc.y += red[w * mc + m].y;
+        }
+        if constexpr (MODE == 0) {
+          __hip_atomic_fetch_add(acc_out + (size_t)(xcc_id() & (kAccRegions - 1)) * T + off + k0 + m,
+                                 pack_sum(acc, scale), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          partial[(size_t)(off + k0 + m) * nblk + blk] = acc;
+        }
+      }
+    }
+  }
+}
+
+template <int RT, int CW, int CTW, int KH, int MODE>
+hipError_t tile_t(hipStream_t s, const SepArgs& a) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile<RT, CW, CTW, KH, MODE>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax);
+  if (attr != hipSuccess) return attr;
+  const TileShape sh{RT, CW, CTW, KH};
+  const size_t lds = tile_lds_bytes(sh, a.sc, a.mmax);
+  if (lds > (size_t)kLdsMax) return hipErrorInvalidValue;
+  if (MODE == 0 && (!a.acc_in || !a.acc_out || !a.acc_zero || a.T < 1)) return hipErrorInvalidValue;
+  dim3 grid(sh.gx(a.nx), sh.gy(a.ny), a.B);
+  hipLaunchKernelGGL((k_tile<RT, CW, CTW, KH, MODE>), grid, dim3(sh.waves() * 64), lds, s, a.coef, a.st_in, a.acc_in,
+                     a.B == 1 ? a.one_m : 0, a.B == 1 ? a.one_off : 0, a.T, a.acc_unscale, a.nx, a.ny, a.sc, a.upd,
+                     a.hd, a.st_out, a.vin, a.hist, a.flag, a.inv_n, a.phase, a.grad, a.partial, a.acc_out, a.acc_zero,
+                     a.acc_scale);
+  return hipGetLastError();
+}
+
+template <int RT, int CW, int CTW, int KH>
+hipError_t tile_mode(hipStream_t s, const SepArgs& a) {
+  switch (a.mode) {
+    case 0: return tile_t<RT, CW, CTW, KH, 0>(s, a);
+    case 1: return tile_t<RT, CW, CTW, KH, 1>(s, a);
+    case 2: return tile_t<RT, CW, CTW, KH, 2>(s, a);
+    case 3: return tile_t<RT, CW, CTW, KH, 3>(s, a);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Figures of merit of `n` consecutive masks of a solve from their V (hist [slot][T]): block (slot, b)
+// writes stats[b][k0 + slot].
+__global__ void __launch_bounds__(256)
+k_stats(const float2* __restrict__ hist, int T, const HoloDesc* __restrict__ hd, const TrapState* __restrict__ st,
+        float* __restrict__ stats, int k0, int stat_stride) {
+  __shared__ float sh[8 * 4];
+  const int b = blockIdx.y, slot = blockIdx.x;
+  const VArray v{reinterpret_cast<const float*>(hist + (size_t)slot * T), hd[b].off};
+  update_traps<256>(v, st, hd[b].off, hd[b].m, 0, sh, stats + 3 * ((size_t)b * stat_stride + k0 + slot), nullptr,
+                    [](int, const TrapState&) {});
+}
+
+}  // namespace
+
+hipError_t launch_stats(hipStream_t s, int n, int B, int T, const float2* hist, const HoloDesc* hd,
+                        const TrapState* st, float* stats, int k0, int stat_stride) {
+  hipLaunchKernelGGL(k_stats, dim3(n, B), dim3(256), 0, s, hist, T, hd, st, stats, k0, stat_stride);
+  return hipGetLastError();
+}
+
+hipError_t launch_tile(hipStream_t s, const SepArgs& a) {
+  if (a.nx < 1 || a.ny < 1 || a.mmax < 1 || a.mmax > kMaxTraps || a.sc < 16 || a.sc % 16 != 0)
+    return hipErrorInvalidValue;
+  switch (a.shape) {
+    case kTile32: return tile_mode<2, 2, 1, 1>(s, a);
+    case kTile32Split: return tile_mode<2, 2, 1, 2>(s, a);
+    case kTile64: return tile_mode<4, 2, 2, 1>(s, a);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace hot

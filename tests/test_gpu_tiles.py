@@ -1,0 +1,133 @@
+"""The tile kernels (the default of the on-the-fly and separable variants) at the edges of their
+blocks, trap tiles and super-chunks, against the FP64 oracle (needs an MI355X).
+
+Bars: the solver's (phase within 1e-3 rad on 99.9 % of pixels, |V| within 1e-4); gradients and trap
+fields of given masks within 2e-6 relative L2: a table entry's FP32 argument is at most 5 revolutions,
+so its rounding is at most 2^-22 revolutions (1.5e-6 rad, far less on average), the hardware sin/cos
+add 1.2e-7 each and the split products 2^-24 each.
+"""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as W
+from tests.parity import as_complex, assert_phase, assert_stats, assert_V, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    print(f"\n[gpu case] {request.node.nodeid}", file=sys.stderr, flush=True)
+    yield
+
+
+# (nx, ny, traps): 32 x 32 blocks with 4 or 8 waves, 64 x 64 blocks (grids of half as many as the
+# compute units), one and several trap tiles and super-chunks, grids off every multiple
+EDGES = [(16, 16, 1), (17, 33, 15), (31, 65, 16), (64, 32, 17), (33, 100, 48), (96, 65, 49), (127, 129, 65),
+         (700, 840, 5), (705, 769, 40), (769, 705, 97)]
+
+
+@pytest.mark.parametrize("nx,ny,m", EDGES)
+def test_gsw_at_block_edges(hot, nx, ny, m):
+    p = W.random_problem(900 + m, nx, ny, m, 2)
+    with hot.Context(0) as c:
+        r = c.hot_gsw(p.slm, p.xyz, p.theta0, p.iters, state=True)
+        q = c.hot_gsw(p.slm, p.xyz, p.theta0, p.iters, stats=False)
+        torch.cuda.synchronize()
+    o = oracle.solve("gsw", p.slm, p.xyz, p.theta0, p.iters)
+    if m * 64 <= nx * ny:  # (more traps than that on so small a mask: the iterations amplify rounding)
+        assert_phase(to_np(r.phase), o["phi"])
+        assert_V(to_np(r.V), o["V"])
+        assert_stats(r.stats, o["stats"])
+    assert torch.equal(r.phase, q.phase) and torch.equal(r.V, q.V)
+
+
+def relative(x, ref):
+    return np.linalg.norm(x - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("nx,ny,counts", [(16, 16, [1, 16]), (33, 31, [17, 3, 33]), (130, 65, [300, 2]),
+                                          (512, 257, [64, 5, 100, 31, 48, 16]), (200, 72, [2048])])
+def test_fields_and_gradients_at_edges(hot, nx, ny, counts):
+    rng = np.random.default_rng(7 * nx + ny)
+    slm, T = W.Slm(nx, ny), int(sum(counts))
+    xyz = W.box_uniform(rng, T)
+    phi = rng.uniform(-40.0, 40.0, (len(counts), ny, nx)).astype(np.float32)
+    G = rng.standard_normal((T, 2)).astype(np.float32)
+    dphi, dG = torch.tensor(phi, device="cuda"), torch.tensor(G, device="cuda")
+    with hot.Context(0) as c:
+        V = c.hot_forward_V(slm, counts, xyz, dphi)
+        g = c.hot_adjoint(slm, counts, xyz, dphi, dG)
+        up = c.hot_adjoint(slm, counts, xyz, dphi, dG * 2.0 ** 60)
+        zero = c.hot_adjoint(slm, counts, xyz, dphi, dG * 0.0)
+        torch.cuda.synchronize()
+    o = 0
+    for b, m in enumerate(counts):
+        flat = phi[b].ravel().astype(np.float64)
+        # V of a mask of random phases is of size 1/sqrt(N): the bar is on the scale of its terms
+        ref = oracle.forward(slm, xyz[o:o + m], flat)
+        assert np.abs(as_complex(to_np(V[o:o + m])) - ref).max() <= 2e-6
+        gr = oracle.adjoint(slm, xyz[o:o + m], flat, G[o:o + m, 0].astype(np.float64) + 1j * G[o:o + m, 1])
+        assert relative(to_np(g[b]).ravel(), np.ravel(gr)) <= 2e-6
+        o += m
+    assert torch.equal(up, g * 2.0 ** 60)  # a power of two in G passes through exactly
+    assert not zero.any()
+
+
+def test_nan_phase_stays_in_its_hologram(hot):
+    slm = W.Slm(70, 40)
+    xyz = W.box_uniform(np.random.default_rng(5), 9)
+    phi = torch.rand(3, 40, 70, device="cuda")
+    phi[1, 13, 21] = float("nan")
+    with hot.Context(0) as c:
+        V = to_np(c.hot_forward_V(slm, [3, 3, 3], xyz, phi))
+    assert np.isnan(V[3:6]).all() and np.isfinite(V[:3]).all() and np.isfinite(V[6:]).all()
+
+
+def test_wide_range_of_weights(hot):
+    """Weights over twelve decades: the largest decide the mask; the split of c_m Y_m is scaled by the
+    largest weight, so none of them overflows the halves."""
+    p = W.random_problem(941, 96, 80, 20)
+    w = np.logspace(-6, 6, 20)
+    w0 = torch.tensor(w, dtype=torch.float32, device="cuda")
+    with hot.Context(0) as c:
+        r = c.hot_gsw(p.slm, p.xyz, p.theta0, 0, w0=w0)
+        torch.cuda.synchronize()
+    ref = oracle.backward(p.slm, p.xyz, to_np(w0), p.theta0)
+    assert_phase(to_np(r.phase), ref)
+
+
+def test_statistics_over_more_masks_than_are_kept(hot):
+    """The figures of merit are taken from V of up to 64 masks at a time; 130 iterations take three
+    turns, and give what the direct-sum kernels (a launch-shape knob set) give mask by mask."""
+    p = W.random_problem(942, 96, 64, 6)
+    with hot.Context(0) as c:
+        a = c.hot_gsw(p.slm, p.xyz, p.theta0, 130)
+        b = c.hot_gsw_noalloc(p.slm, p.xyz, p.theta0, 130)
+        c.set_tuning(rows=1)
+        d = c.hot_gsw(p.slm, p.xyz, p.theta0, 130)
+        torch.cuda.synchronize()
+    np.testing.assert_array_equal(a.stats, b.stats)
+    assert_stats(a.stats, d.stats)
+
+
+def test_changing_kernels_on_one_context(hot):
+    """Launch-shape knobs select the direct-sum kernels; the tables of one choice are not reused for
+    the other, and the first result comes back."""
+    p = W.random_problem(943, 150, 90, 24, 3)
+    with hot.Context(0) as c:
+        a = c.hot_gsw(p.slm, p.xyz, p.theta0, 3)
+        c.set_tuning(rows=1)
+        b = c.hot_gsw(p.slm, p.xyz, p.theta0, 3)
+        c.set_tuning()
+        d = c.hot_gsw(p.slm, p.xyz, p.theta0, 3)
+        torch.cuda.synchronize()
+    assert torch.equal(a.phase, d.phase) and torch.equal(a.V, d.V)
+    o = oracle.solve("gsw", p.slm, p.xyz, p.theta0, 3)
+    for r in (a, b):
+        assert_phase(to_np(r.phase), o["phi"])
+        assert_V(to_np(r.V), o["V"])
