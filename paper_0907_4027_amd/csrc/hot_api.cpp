@@ -264,7 +264,7 @@ struct Plan {
   int sep_w = 4, nblk_sep = 0, sep_sc = 16;
   // tile kernels: whether they run, block shape (index into kTileShapes), traps per LDS super-chunk
   bool tiles = false;
-  int tile = 0, tile_mc = 16, nblk_tile = 0;
+  int tile = 0, tile_mc = 16, tile_occ = 1, nblk_tile = 0;
   int sep_kh = 1;  // waves per 16 x 16 tile in the separable iteration (2: each takes half of the traps)
   // fused paths' fixed point: scale 2^s with s = 30 - ceil(log2 N) (re and im as 32-bit integers in
   // one 64-bit word); every block sum and every trap's total has magnitude <= N, so no sum of the
@@ -292,30 +292,29 @@ bool use_tiles(const hot_ctx* c, int variant) {
 }
 
 // Block shape and super-chunk of the tile kernels.
-//   64 x 64 pixels (8 waves) once such blocks number at least half of the compute units: their table
-//   work per pixel is half of a 32 x 32 block's (GSW 1024^2 x 256: 24.8 against 42.7 us per iteration;
-//   768^2 x 81, 144 blocks: 15.1 against 20.5 us), while a grid with fewer leaves units idle (512^2 x
-//   100, 64 blocks: 12.2 against 7.5 us).
+//   64 x 64 pixels (k_wide) once such blocks number at least half of the compute units: per pixel they
+//   build half of the table entries of 32 x 32 blocks (GSW 1024^2 x 256: 18.5 against 42.7 us per
+//   iteration; 768^2 x 81, 144 blocks: 13 against 20.5 us), while a grid with fewer leaves units idle
+//   (641 x 479 x 37, 88 blocks: 13.2 against 12.4 us; 512^2 x 100, 64 blocks: 12.2 against 7.5 us).
 //   Else 32 x 32: four waves, or eight (two sharing each 16 x 16 tile, half of the traps each) for more
 //   than 48 traps on a grid of at most one block per unit, where a second wave per SIMD hides latency
 //   (512^2 x 100: 7.5 against 8.2 us); with fewer traps or two resident blocks the exchange of the
 //   partial sums costs more than it hides (641 x 479 x 37: 12.8 against 12.4 us).
-// All traps at once where their tables fit the LDS; on a grid of more blocks than units half of the LDS,
-// so that two blocks share a unit and one's table building overlaps the other's matrix products
-// (2048^2 x 1000: 307 against 340 us per iteration, 64 holograms of 512^2: 222 against 259 us).
+// All traps at once where their tables fit the LDS (up to 256 in k_wide); on a grid of more blocks than
+// units half of the LDS, so that two blocks share a unit and one's vector work overlaps the other's
+// matrix products (k_wide's comment has both sides).
 void choose_tile(const hot_ctx* c, Plan& P) {
   auto blocks = [&](int shape) { return (int64_t)kTileShapes[shape].gx(P.nx) * kTileShapes[shape].gy(P.ny) * P.B; };
-  if (2 * blocks(kTile64) >= c->num_cu) {
-    P.tile = kTile64;
-  } else {
-    P.tile = P.mmax > 48 && blocks(kTile32) <= c->num_cu ? kTile32Split : kTile32;
-  }
+  const bool wide = 2 * blocks(kTileWide) >= c->num_cu;
+  P.tile = wide ? kTileWide : P.mmax > 48 && blocks(kTile32) <= c->num_cu ? kTile32Split : kTile32;
   const TileShape& t = kTileShapes[P.tile];
   P.nblk_tile = t.gx(P.nx) * t.gy(P.ny);
+  P.tile_occ = blocks(P.tile) > c->num_cu ? 2 : 1;
+  const size_t budget = (size_t)kLdsMax / P.tile_occ;
+  auto lds = [&](int mc) { return wide ? wide_lds_bytes(mc, P.mmax) : tile_lds_bytes(t, mc, P.mmax); };
   const int mp = (P.mmax + 15) / 16 * 16;
-  const size_t budget = (size_t)kLdsMax / (blocks(P.tile) > c->num_cu ? 2 : 1);
-  int mc = mp;
-  while (mc > 16 && tile_lds_bytes(t, mc, P.mmax) > budget) mc -= 16;
+  int mc = wide ? std::min(mp, kWideTraps) : mp;
+  while (mc > 16 && lds(mc) > budget) mc -= 16;
   const int nsc = (mp + mc - 1) / mc;  // equal super-chunks
   P.tile_mc = ((mp + nsc - 1) / nsc + 15) / 16 * 16;
 }
@@ -607,6 +606,7 @@ SepArgs sep_args(hot_ctx* c, const Plan& P, int mode, float* phase, int K) {
 SepArgs tile_args(hot_ctx* c, const Plan& P, int mode, float* phase, int K) {
   SepArgs a = sep_args(c, P, mode, phase, K);
   a.shape = P.tile;
+  a.occ = P.tile_occ;
   a.sc = P.tile_mc;
   return a;
 }
@@ -736,7 +736,7 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
     std::vector<uint64_t> key = {(uint64_t)B, (uint64_t)P.T, (uint64_t)P.nx, (uint64_t)P.ny, (uint64_t)K,
                                  (uint64_t)algo, (uint64_t)variant, (uint64_t)P.fract, (uint64_t)P.nt, (uint64_t)P.q,
                                  (uint64_t)P.tpl, (uint64_t)P.fg.seg_w, (uint64_t)P.sep_w, (uint64_t)P.sep_sc, (uint64_t)P.sep_kh,
-                                 (uint64_t)P.rows, (uint64_t)tiles, (uint64_t)want, (uint64_t)(uintptr_t)c->hist.p, (uint64_t)P.tile, (uint64_t)P.tile_mc, (uint64_t)(uintptr_t)phase,
+                                 (uint64_t)P.rows, (uint64_t)tiles, (uint64_t)want, (uint64_t)(uintptr_t)c->hist.p, (uint64_t)P.tile, (uint64_t)P.tile_occ, (uint64_t)P.tile_mc, (uint64_t)(uintptr_t)phase,
                                  (uint64_t)(uintptr_t)V, (uint64_t)(uintptr_t)w_out, (uint64_t)(uintptr_t)theta_out,
                                  (uint64_t)(uintptr_t)c->coef.p, (uint64_t)(uintptr_t)c->st.p,
                                  (uint64_t)(uintptr_t)c->hd.p, (uint64_t)(uintptr_t)c->partial.p,
@@ -1062,6 +1062,7 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   if (P.tiles) {
     SepArgs a;
     a.shape = P.tile;
+    a.occ = P.tile_occ;
     a.sc = P.tile_mc;
     a.B = 1;
     a.nx = P.nx;

@@ -163,6 +163,7 @@ hipError_t launch_forward_stored(hipStream_t s, int n, int B, int mmax, const fl
 // factors are computed in LDS from coef.
 struct SepArgs {
   int shape = 0;  // tile kernels: index into kTileShapes
+  int occ = 1;    // kTileWide: blocks per compute unit (1 or 2)
   int mode = 0;  // 0 iteration, 1 trap pass from `phase`, 2 pixel pass, 3 adjoint (G in vin, grad out)
   int W = 4;     // tiles per block: a block covers 16 rows x 16 W columns
   int kh = 1;    // mode 0: waves per tile (1, or 2 taking half of the traps each)
@@ -216,8 +217,8 @@ struct TileShape {
   constexpr int gx(int nx) const { return (nx + cols() - 1) / cols(); }
   constexpr int gy(int ny) const { return (ny + rows() - 1) / rows(); }
 };
-enum { kTile32 = 0, kTile32Split = 1, kTile64 = 2 };
-constexpr TileShape kTileShapes[] = {{2, 2, 1, 1}, {2, 2, 1, 2}, {4, 2, 2, 1}};
+enum { kTile32 = 0, kTile32Split = 1, kTileWide = 2 };
+constexpr TileShape kTileShapes[] = {{2, 2, 1, 1}, {2, 2, 1, 2}, {4, 1, 4, 2}};  // (the last: k_wide)
 constexpr int kTileFragWords = 528;  // words of a 16 x 16 table fragment
 // dynamic LDS for super-chunks of mc traps (a multiple of 16): fragments of the column table, of the
 // weighted row table (both split) and of the row table (FP32), group constants, trap sums, the
@@ -226,6 +227,13 @@ inline size_t tile_lds_bytes(const TileShape& t, int mc, int mmax) {
   const size_t mp = (size_t)(mmax + 15) / 16 * 16, ct = t.cw * t.ctw, rt = t.rt;
   return (size_t)(mc / 16) * (4 * kTileFragWords * (ct + rt) + 2048 * rt) + (size_t)mc * (16 * (ct + rt) + 8 * t.rt * t.cw) +
          8 * mp + 8 * (size_t)t.waves() + (t.kh > 1 ? 2048 * (size_t)t.waves() * t.ctw : 0);
+}
+// The wide kernel: most traps per super-chunk, and its dynamic LDS for super-chunks of mc traps (the
+// column table, 16 KB that serve in turn, row constants, the weights of all traps, per-wave words)
+constexpr int kWideTraps = 256;
+inline size_t wide_lds_bytes(int mc, int mmax) {
+  const size_t mp = (size_t)(mmax + 15) / 16 * 16;
+  return (size_t)(mc / 16) * 4 * 4 * kTileFragWords + 16384 + (size_t)mc * (4 * 8 + 4) + 8 * mp + 64;
 }
 hipError_t launch_tile(hipStream_t s, const SepArgs& a);
 // Figures of merit of n consecutive masks from their V (hist [n][T]) into stats[b][k0 ..].

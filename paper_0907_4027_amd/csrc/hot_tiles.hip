@@ -32,9 +32,8 @@
 //               lane groups are summed.
 //
 // What bounds it.  One iteration of 1024^2 x 256 is 8.6 GFLOP of products (5.1 us at the rate of the
-// halves) and 24.8 us per launch, against 110 us of the direct sums; 512^2 x 100 takes 7.5 us (15.9).
-// On the larger grid the rest is building the tables (twice per block: traps go through the LDS in
-// super-chunks), on the smaller latency: 1.1 us from one launch to the next, 1.2 us until the first
+// halves) and 18.5 us per launch (k_wide), against 110 us of the direct sums; 512^2 x 100 takes 7.5 us
+// (15.9).  On the larger grid it is vector work beside the products (k_wide), on the smaller latency: 1.1 us from one launch to the next, 1.2 us until the first
 // coefficients are there, 1.2 us for the last trap sums to be added, and between them phases of a few
 // hundred instructions per wave at one or two waves per SIMD.
 #include "hot_device.h"
@@ -118,6 +117,98 @@ __device__ __forceinline__ float sum_groups(float2 a, float2 b) {
 // and with 132 words per group of four traps both kinds of access reach every bank evenly.
 constexpr int kFragWords = kTileFragWords;
 constexpr int kTqWords = 132, kLoWords = 64;
+
+// E = S / |S|, 1 where S = 0 (arg 0 = 0), 0 outside the grid.  S is a sum of products of halves,
+// multiples of 2^-48, over weights scaled to at most 1: |S|^2 neither underflows nor overflows.
+__device__ __forceinline__ void unit_of(float x, float y, bool in, float& er, float& ei) {
+  const float n2 = __builtin_fmaf(x, x, y * y);
+  const float inv = __builtin_amdgcn_rsqf(n2);
+  const bool zero = n2 == 0.0f;
+  er = in ? (zero ? 1.0f : x * inv) : 0.0f;
+  ei = in && !zero ? y * inv : 0.0f;
+}
+
+// sum over the lane's four rows of conj(y) t
+__device__ __forceinline__ float2 fold_rows(const float2 (&y)[4], const f32x4& tre, const f32x4& tim) {
+  float pr[2], pi[2];  // over rows (0, 1) and (2, 3)
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float2 a = y[2 * h], c = y[2 * h + 1];
+    const float tr0 = tre[2 * h], ti0 = tim[2 * h], tr1 = tre[2 * h + 1], ti1 = tim[2 * h + 1];
+    pr[h] = __builtin_fmaf(c.x, tr1, __builtin_fmaf(c.y, ti1, __builtin_fmaf(a.x, tr0, a.y * ti0)));
+    pi[h] = __builtin_fmaf(c.x, ti1, __builtin_fmaf(-c.y, tr1, __builtin_fmaf(a.x, ti0, -a.y * tr0)));
+  }
+  return make_float2(pr[0] + pr[1], pi[0] + pi[1]);
+}
+
+// The state and (MODE 0) V's words of trap threadIdx.x, loaded by the constructor and used by
+// weights(): the accumulators were rewritten by the previous launch and come from beyond the L2, so the
+// tables are built while these loads are in flight.
+template <int NT, int MODE>
+struct TrapInputs {
+  static constexpr int NW = NT / 64;
+  VAcc vacc;
+  int off, M;
+  TrapState s_first = {0.0f, 0.0f, 0.0f, 0.0f};
+  unsigned long long w_first[kAccRegions] = {};
+  __device__ __forceinline__ TrapInputs(const TrapState* st_in, const unsigned long long* acc_in, int T, int off_,
+                                        int M_, float unscale)
+      : vacc{acc_in, T, off_, unscale}, off(off_), M(M_) {
+    const int tm = min((int)threadIdx.x, M - 1);
+    if (MODE != 1 && MODE != 3 && __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63) < M) {
+      s_first = st_in[off + tm];
+      if (MODE == 0) vacc.load(tm, w_first);  // (acc_in is valid even when upd == 0)
+    }
+  }
+  // c_m of all traps into cw [Mp] (after the GS/GSW update where upd asks for it; the lead block also
+  // writes the new state and keeps V in hist); returns the exponent that scales the largest below 1.
+  // Ends with a barrier; sh: 2 NW floats.
+  __device__ __forceinline__ int weights(float2* cw, float* sh, int Mp, const TrapState* st_in, const float* vin,
+                                         int upd, bool lead, TrapState* st_out, float2* hist, int* flag) const {
+    const int wave = threadIdx.x >> 6;
+    float wmax = 0.0f;
+    for (int m = M + (int)threadIdx.x; m < Mp; m += NT) cw[m] = make_float2(0.0f, 0.0f);
+    if (MODE == 3) {
+      for (int m = threadIdx.x; m < M; m += NT) {
+        const float2 gm = make_float2(vin[2 * (off + m)], vin[2 * (off + m) + 1]);
+        cw[m] = gm;
+        wmax = fmaxf(wmax, fmaxf(fabsf(gm.x), fabsf(gm.y)));
+      }
+    } else if (MODE == 2 || upd == 0) {
+      for (int m = threadIdx.x; m < M; m += NT) {
+        const TrapState s = m == (int)threadIdx.x ? s_first : st_in[off + m];
+        cw[m] = trap_weight(s);
+        wmax = fmaxf(wmax, fabsf(s.w));
+      }
+    } else {
+      unsigned long long w8[kAccRegions];
+#pragma unroll
+      for (int q = 0; q < kAccRegions; ++q) {
+        w8[q] = w_first[q];
+        asm volatile("" : "+v"(w8[q]));  // (the sum stays here)
+      }
+      const float2 v_first = vacc.sum(w8);
+      if (lead && hist != nullptr) {
+        if ((int)threadIdx.x < M) hist[off + threadIdx.x] = v_first;
+        for (int m = NT + (int)threadIdx.x; m < M; m += NT) hist[off + m] = vacc(m);
+      }
+      auto emit = [&](int m, const TrapState& st) {
+        if (lead) st_out[off + m] = st;
+        cw[m] = trap_weight(st);
+        wmax = fmaxf(wmax, fabsf(st.w));
+      };
+      update_traps<NT, VAcc, decltype(emit), true>(vacc, st_in, off, M, upd, sh, nullptr, lead ? flag : nullptr, emit,
+                                                   v_first, s_first);
+    }
+    wmax = wave_max(wmax);
+    if ((threadIdx.x & 63) == 0) sh[NW + wave] = wmax;
+    __syncthreads();
+    wmax = sh[NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) wmax = fmaxf(wmax, sh[NW + w]);
+    return __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(wmax));
+  }
+};
 
 // MODE 0: one iteration: GS/GSW update (upd 1 / 2, recomputed by every block from the previous mask's
 //   fixed-point sums acc_in; 0: st_in as is), pixel pass, trap pass; the phase is written when not null.
@@ -270,18 +361,10 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 
   const int nsc = (Mp + mc - 1) / mc;
   const int n0 = min(mc, Mp), nt0 = n0 >> 4;
-  const VAcc vacc{acc_in, T, off, unscale};
   const bool lead = blockIdx.x == 0 && blockIdx.y == 0;
-  const bool holds = wave * 64 < M;  // the wave holds traps
-  const int tm = min((int)threadIdx.x, M - 1);
-  TrapState s_first = {0.0f, 0.0f, 0.0f, 0.0f};
-  unsigned long long w_first[kAccRegions] = {};
   stage_refs(0, n0);
   __builtin_amdgcn_sched_barrier(0);
-  if (kPixel && MODE != 3 && holds) {
-    s_first = st_in[off + tm];
-    if (MODE == 0) vacc.load(tm, w_first);
-  }
+  const TrapInputs<NT, MODE> in(st_in, acc_in, T, off, M, unscale);
   __builtin_amdgcn_sched_barrier(0);
   for (int tt = jx; tt < nt0; tt += XS) put_x(tt);
   constexpr int YK = 4;  // this wave's first row fragments stay in registers until the weights are known
@@ -314,43 +397,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
   auto inside = [&](int ct, int v) { return r < ny && c0 + 16 * ct + v < nx; };
 
   if constexpr (kPixel) {
-    float wmax = 0.0f;
-    for (int m = M + (int)threadIdx.x; m < Mp; m += NT) cw[m] = make_float2(0.0f, 0.0f);
-    if (MODE == 3) {
-      for (int m = threadIdx.x; m < M; m += NT) {
-        const float2 gm = make_float2(vin[2 * (off + m)], vin[2 * (off + m) + 1]);
-        cw[m] = gm;
-        wmax = fmaxf(wmax, fmaxf(fabsf(gm.x), fabsf(gm.y)));
-      }
-    } else if (MODE == 2 || upd == 0) {
-      for (int m = threadIdx.x; m < M; m += NT) {
-        const TrapState s = m == (int)threadIdx.x ? s_first : st_in[off + m];
-        cw[m] = trap_weight(s);
-        wmax = fmaxf(wmax, fabsf(s.w));
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < kAccRegions; ++q) asm volatile("" : "+v"(w_first[q]));  // (the sum stays here)
-      const float2 v_first = vacc.sum(w_first);
-      if (lead && hist != nullptr) {
-        if ((int)threadIdx.x < M) hist[off + threadIdx.x] = v_first;
-        for (int m = NT + (int)threadIdx.x; m < M; m += NT) hist[off + m] = vacc(m);
-      }
-      auto emit = [&](int m, const TrapState& st) {
-        if (lead) st_out[off + m] = st;
-        cw[m] = trap_weight(st);
-        wmax = fmaxf(wmax, fabsf(st.w));
-      };
-      update_traps<NT, VAcc, decltype(emit), true>(vacc, st_in, off, M, upd, sh, nullptr, lead ? flag : nullptr, emit,
-                                                   v_first, s_first);
-    }
-    wmax = wave_max(wmax);
-    if (lane == 0) sh[NW + wave] = wmax;
-    __syncthreads();
-    wmax = sh[NW];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) wmax = fmaxf(wmax, sh[NW + w]);
-    wexp = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(wmax));
+    wexp = in.weights(cw, sh, Mp, st_in, vin, upd, lead, st_out, hist, flag);
     // weighted Y of the first super-chunk
 #pragma unroll
     for (int j = 0; j < YK; ++j) {
@@ -452,14 +499,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
           float er[4], ei[4];
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            // E = S / |S|, 1 where S = 0 (arg 0 = 0).  S is a sum of products of halves, multiples of
-            // 2^-48, over weights scaled to at most 1: |S|^2 neither underflows nor overflows.
-            const float x = sre[ct][v], y = sim[ct][v];
-            const float n2 = __builtin_fmaf(x, x, y * y);
-            const float inv = __builtin_amdgcn_rsqf(n2);
-            const bool in = inside(ct, v), zero = n2 == 0.0f;
-            er[v] = in ? (zero ? 1.0f : x * inv) : 0.0f;
-            ei[v] = in && !zero ? y * inv : 0.0f;
+            unit_of(sre[ct][v], sim[ct][v], inside(ct, v), er[v], ei[v]);
           }
           put_e(ct, er, ei);
         }
@@ -520,15 +560,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
         for (int p = 0; p < 2; ++p) {
           float2 yv[4];
           get_y(rt * ntm + min(tt + p, t1 - 1), yv);
-          float pr[2], pi[2];  // Re and Im of conj(y) t over rows (0, 1) and (2, 3)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const float2 a = yv[2 * h], c = yv[2 * h + 1];
-            const float tr0 = tre[p][2 * h], ti0 = tim[p][2 * h], tr1 = tre[p][2 * h + 1], ti1 = tim[p][2 * h + 1];
-            pr[h] = __builtin_fmaf(c.x, tr1, __builtin_fmaf(c.y, ti1, __builtin_fmaf(a.x, tr0, a.y * ti0)));
-            pi[h] = __builtin_fmaf(c.x, ti1, __builtin_fmaf(-c.y, tr1, __builtin_fmaf(a.x, ti0, -a.y * tr0)));
-          }
-          q[p] = make_float2(pr[0] + pr[1], pi[0] + pi[1]);
+          q[p] = fold_rows(yv, tre[p], tim[p]);
         }
         const float v = sum_groups(q[0], q[1]);
         if (tt + (g & 1) < t1) rw[32 * (tt + (g & 1))] = v;
@@ -538,6 +570,350 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
         float2 acc = red[m];
 #pragma unroll
         for (int w = 1; w < NS; ++w) {
+          acc.x += red[w * mc + m].x;
+          acc.y += red[w * mc + m].y;
+        }
+        if constexpr (MODE == 0) {
+          __hip_atomic_fetch_add(acc_out + (size_t)(xcc_id() & (kAccRegions - 1)) * T + off + k0 + m,
+                                 pack_sum(acc, scale), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          partial[(size_t)(off + k0 + m) * nblk + blk] = acc;
+        }
+      }
+    }
+  }
+}
+
+// The same for large grids: 64 x 64 pixels per block, eight waves.  What differs from k_tile is where
+// the row factor lives.  A wave multiplies one row tile by all four column tiles, for half of the trap
+// tiles (part 0 the even ones, part 1 the odd ones), so no other wave needs its weighted row entries:
+// it computes them in registers, in the layout of the matrix operand (lane = row, four traps), between
+// the products of the previous trap tile.  Only the column table stands in LDS, which then holds it for
+// up to 256 traps at once: no super-chunks, no rebuilding and no barriers between them up to that count.
+// The two partial sums of a tile meet through LDS, each wave finishing two of the four column tiles; in
+// the trap pass it takes those two for all traps, with the row entries (lane = trap, four rows) in
+// registers again.
+//
+// OCC: blocks that share a compute unit (1: up to 256 registers per wave; 2: up to 128, with half of the
+// LDS each, so that one block's vector work overlaps the other's products).  Per iteration, against
+// k_tile with 64 x 64 pixels per block: GSW 1024^2 x 256 24.2 -> 18.5 us (OCC 1; 19.7 with the
+// registers of OCC 2), 2048^2 x 1000 305 -> 259 us (OCC 2; 285 with OCC 1), 64 holograms of 512^2 with
+// 4..256 traps 195 -> 168 us (OCC 2; 191).  What bounds it: at 1024^2 x 256 about 38000 cycles, of which
+// 9300 in the pixel pass and 11900 in the trap pass are at the issue rate of their vector instructions
+// (4.5 cycles each, and 8 per product), 6500 build the column table while V is on its way, the rest is
+// latency (update, exchange, barriers, last sums).
+template <int MODE, int OCC>
+__global__ void __launch_bounds__(512, 2 * OCC)
+k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
+       const unsigned long long* __restrict__ acc_in, int one_m, int one_off, int T, float unscale, int nx, int ny,
+       int mc, int upd, const HoloDesc* __restrict__ hd, TrapState* __restrict__ st_out,
+       const float* __restrict__ vin, float2* __restrict__ hist, int* __restrict__ flag, float inv_n,
+       float* __restrict__ phase, float* __restrict__ grad, float2* __restrict__ partial,
+       unsigned long long* __restrict__ acc_out, unsigned long long* __restrict__ acc_zero, float scale) {
+  constexpr int NW = 8, NT = 512, CT = 4;
+  constexpr bool kPixel = MODE != 1, kTrap = MODE <= 1;
+  extern __shared__ float4 lds4[];
+  const int b = blockIdx.z;
+  int M = one_m, off = one_off;
+  if (one_m <= 0) {
+    M = hd[b].m;
+    off = hd[b].off;
+  }
+  const int Mp = (M + 15) & ~15;
+  const int ntm = mc >> 4;
+  unsigned* xf = reinterpret_cast<unsigned*>(lds4);                      // [ntm][CT] X fragments
+  float4* sx = reinterpret_cast<float4*>(xf + ntm * CT * kFragWords);     // 16 KB: column constants while the
+  float2* red = reinterpret_cast<float2*>(sx);                            //   table is built, partial pixel sums,
+  float4* rx = sx + (int)(threadIdx.x >> 6) * 128;                        //   trap sums [NW][mc]
+  float2* rk = reinterpret_cast<float2*>(sx + 1024);                      // [4][mc] row constants {K, s}
+  float* qv = reinterpret_cast<float*>(rk + 4 * mc);                      // [mc] curvature q
+  float2* cw = reinterpret_cast<float2*>(qv + mc);                        // [Mp] c_m
+  float* sh = reinterpret_cast<float*>(cw + Mp);                          // [2 NW]
+
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+  const int rt = wave & 3, part = wave >> 2;
+  const int row0 = blockIdx.y * 64, cb = blockIdx.x * 64;
+  const int r = row0 + 16 * rt + li;
+  const int c0 = cb + 32 * part + 4 * g;  // the lane's first column of the first tile it finishes
+  const size_t pix0 = (size_t)b * nx * ny + (size_t)r * nx + c0;
+  const int ewofs = 16 * g + kTqWords * (li >> 2) + (li & 3);  // entry (4 g + v, trap li): + 4 v
+  const int pofs = 4 * li + kTqWords * g;                      // entries (li, traps 4 g .. 4 g + 3)
+  const float fr = (float)(li - 8), frq = fr * fr;
+  float fi[4], fq[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    fi[v] = (float)(4 * g + v - 8);
+    fq[v] = fi[v] * fi[v];
+  }
+
+  // tables of the traps [k0, k0 + n): this wave fills column tile rt for the trap tiles part, part + 2,
+  // ..., and forms the constants of column tile rt (for itself) and row tile rt (for all waves) of their
+  // traps.  Lane group g takes the column (g even) or row constants (g odd) of trap tile
+  // part + 2 (g / 2 + 2 round).
+  const double Cg = g & 1 ? (double)(2 * (row0 + 16 * rt + 8) - (ny - 1)) : (double)(2 * (cb + 16 * rt + 8) - (nx - 1));
+  struct RefCoef {
+    double lin, q;
+  };
+  auto ref_load = [&](int k0, int round) {
+    const TrapCoef* k = coef + off + min(k0 + 16 * (part + 2 * ((g >> 1) + 2 * round)) + li, M - 1);
+    return RefCoef{g & 1 ? k->b : k->a, k->g};
+  };
+  auto ref_store = [&](const RefCoef& c, int n, int round) {
+    const int i = (g >> 1) + 2 * round, m = 16 * (part + 2 * i) + li;
+    if (m >= n) return;
+    const double kk = __builtin_fma(c.q, Cg * Cg, c.lin * Cg);
+    double sl = __builtin_fma(4.0 * c.q, Cg, 2.0 * c.lin);
+    sl -= __builtin_rint(sl);
+    double q = 4.0 * c.q;
+    q -= __builtin_rint(q);
+    const float2 ks = make_float2((float)(kk - __builtin_floor(kk)), (float)sl);
+    if (g & 1) {
+      rk[rt * mc + m] = ks;
+    } else {
+      rx[16 * i + li] = make_float4(ks.x, ks.y, (float)q, 0.0f);
+      if (rt == 0) qv[m] = (float)q;
+    }
+  };
+  auto build = [&](const RefCoef& first, int k0, int n) {
+    const int nt = n >> 4;
+    ref_store(first, n, 0);
+    for (int round = 1; part + 4 * round < nt; ++round) ref_store(ref_load(k0, round), n, round);
+#pragma unroll 2
+    for (int tt = part; tt < nt; tt += 2) {
+      const int i = tt >> 1;
+      const float4 k = rx[16 * i + li];
+      unsigned* x = xf + (tt * CT + rt) * kFragWords + ewofs;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float t = __builtin_fmaf(k.z, fq[v], __builtin_fmaf(k.y, fi[v], k.x));
+        const Split s = split(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+        x[4 * v] = s.hi;
+        x[4 * v + kLoWords] = s.lo;
+      }
+    }
+  };
+
+  const int nsc = (Mp + mc - 1) / mc;
+  const int n0 = min(mc, Mp);
+  const bool lead = blockIdx.x == 0 && blockIdx.y == 0;
+  const RefCoef c_first = ref_load(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  const TrapInputs<NT, MODE> in(st_in, acc_in, T, off, M, unscale);
+  __builtin_amdgcn_sched_barrier(0);
+  build(c_first, 0, n0);
+
+  u32x4 eh[2], el[2], fh[2], fl[2];  // E = (Er, Ei) hi, lo and (Ei, -Er) hi, lo of the two tiles
+  auto put_e = [&](int ct, const float* er, const float* ei) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const Split s = split(er[v], ei[v]);
+      eh[ct][v] = s.hi;
+      el[ct][v] = s.lo;
+      fh[ct][v] = turn_m(s.hi);
+      fl[ct][v] = turn_m(s.lo);
+    }
+  };
+  auto inside = [&](int ct, int v) { return r < ny && c0 + 16 * ct + v < nx; };
+
+  if constexpr (kPixel) {
+    const int wexp = in.weights(cw, sh, Mp, st_in, vin, upd, lead, st_out, hist, flag);
+    for (int m = threadIdx.x; m < M; m += NT) {  // (each thread rescales the weights it wrote)
+      const float2 c = cw[m];
+      cw[m] = make_float2(__builtin_amdgcn_ldexpf(c.x, -wexp), __builtin_amdgcn_ldexpf(c.y, -wexp));
+    }
+    __syncthreads();
+    if (MODE == 0 && lead) {
+      for (int m = threadIdx.x; m < M; m += NT) {
+#pragma unroll
+        for (int q = 0; q < kAccRegions; ++q) acc_zero[(size_t)q * T + off + m] = 0ull;
+      }
+    }
+
+    f32x4 sre[CT], sim[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      sre[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      sim[ct] = sre[ct];
+    }
+    struct RowOps {
+      u32x4 bh, bl, ch, cl;
+    };
+    auto row_ops = [&](int k0, int tt) {  // c_m Y_m(row li) of traps 16 tt + 4 g .. + 3: (wr, -wi) and (wi, wr)
+      const float4* k4 = reinterpret_cast<const float4*>(rk + rt * mc + 16 * tt + 4 * g);
+      const float4* c4 = reinterpret_cast<const float4*>(cw + k0 + 16 * tt + 4 * g);
+      const float4 q4 = *reinterpret_cast<const float4*>(qv + 16 * tt + 4 * g);
+      const float4 ka = k4[0], kb = k4[1], ca = c4[0], cc = c4[1];
+      const float K[4] = {ka.x, ka.z, kb.x, kb.z}, S[4] = {ka.y, ka.w, kb.y, kb.w}, Q[4] = {q4.x, q4.y, q4.z, q4.w};
+      const float cx[4] = {ca.x, ca.z, cc.x, cc.z}, cy[4] = {ca.y, ca.w, cc.y, cc.w};
+      RowOps o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float t = __builtin_fmaf(Q[e], frq, __builtin_fmaf(S[e], fr, K[e]));
+        const float yr = __builtin_amdgcn_cosf(t), yi = __builtin_amdgcn_sinf(t);
+        const Split s = split_conj(__builtin_fmaf(cx[e], yr, -cy[e] * yi), __builtin_fmaf(cx[e], yi, cy[e] * yr));
+        o.bh[e] = s.hi;
+        o.bl[e] = s.lo;
+        o.ch[e] = turn_p(s.hi);
+        o.cl[e] = turn_p(s.lo);
+      }
+      return o;
+    };
+    for (int s = 0; s < nsc; ++s) {
+      const int k0 = s * mc, n = min(mc, Mp - k0), nt = n >> 4;
+      if (s > 0) {
+        const RefCoef c = ref_load(k0, 0);
+        __syncthreads();  // the previous super-chunk is no longer read
+        build(c, k0, n);
+        __syncthreads();
+      }
+      if (part < nt) {
+        RowOps o = row_ops(k0, part);
+        for (int tt = part; tt < nt; tt += 2) {
+          const RowOps next = row_ops(k0, min(tt + 2, nt - 1));  // (the last one is not used)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const unsigned* xb = xf + (tt * CT + ct) * kFragWords + pofs;
+            const u32x4 ah = *reinterpret_cast<const u32x4*>(xb), al = *reinterpret_cast<const u32x4*>(xb + kLoWords);
+            sre[ct] = mfma32(ah, o.bh, sre[ct]);
+            sim[ct] = mfma32(ah, o.ch, sim[ct]);
+            sre[ct] = mfma32(ah, o.bl, sre[ct]);
+            sim[ct] = mfma32(ah, o.cl, sim[ct]);
+            sre[ct] = mfma32(al, o.bh, sre[ct]);
+            sim[ct] = mfma32(al, o.ch, sim[ct]);
+          }
+          o = next;
+        }
+      }
+    }
+    // the two partial sums: a wave gives the tiles it does not finish to the other, one at a time
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const f32x4 gr = part == 0 ? sre[2 + i] : sre[i], gi = part == 0 ? sim[2 + i] : sim[i];
+      if (i > 0) __syncthreads();
+      float4* p = sx + wave * 128 + lane;
+      p[0] = make_float4(gr[0], gr[1], gr[2], gr[3]);
+      p[64] = make_float4(gi[0], gi[1], gi[2], gi[3]);
+      __syncthreads();
+      const float4* o = sx + (wave ^ 4) * 128 + lane;
+      const float4 a = o[0], c = o[64];
+      const f32x4 ra = {a.x, a.y, a.z, a.w}, ia = {c.x, c.y, c.z, c.w};
+      if (part == 0) {
+        sre[i] += ra;
+        sim[i] += ia;
+      } else {
+        sre[i] = sre[2 + i] + ra;
+        sim[i] = sim[2 + i] + ia;
+      }
+    }
+    if constexpr (MODE == 3) {
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if (inside(ct, v)) {
+            const size_t px = pix0 + 16 * ct + v;
+            const float pr = caller_phase_rev(phase[px]);
+            grad[px] = __builtin_amdgcn_ldexpf(
+                inv_n * (__builtin_amdgcn_cosf(pr) * sim[ct][v] - __builtin_amdgcn_sinf(pr) * sre[ct][v]), wexp);
+          }
+        }
+      }
+    } else {
+      if (phase != nullptr) {  // (the last mask of a solve)
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (inside(ct, v)) phase[pix0 + 16 * ct + v] = phase_of(sim[ct][v], sre[ct][v]);
+        }
+      }
+      if constexpr (kTrap) {
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+          float er[4], ei[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) unit_of(sre[ct][v], sim[ct][v], inside(ct, v), er[v], ei[v]);
+          put_e(ct, er, ei);
+        }
+      }
+    }
+    if constexpr (kTrap) __syncthreads();  // (the trap sums take the place of the partial sums)
+  } else {
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+      float er[4], ei[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool in = inside(ct, v);
+        const float pr = in ? caller_phase_rev(phase[pix0 + 16 * ct + v]) : 0.0f;
+        er[v] = in ? __builtin_amdgcn_cosf(pr) : 0.0f;
+        ei[v] = in ? __builtin_amdgcn_sinf(pr) : 0.0f;
+      }
+      put_e(ct, er, ei);
+    }
+    __syncthreads();
+  }
+
+  if constexpr (kTrap) {
+    const int nblk = gridDim.x * gridDim.y, blk = blockIdx.y * gridDim.x + blockIdx.x;
+    // super-chunks: the one whose table is in LDS first
+    for (int j = 0; j < nsc; ++j) {
+      const int s = kPixel ? nsc - 1 - j : j;
+      const int k0 = s * mc, n = min(mc, Mp - k0), nt = n >> 4;
+      if (j > 0) {
+        const RefCoef c = ref_load(k0, 0);
+        __syncthreads();  // the previous super-chunk's table and sums are no longer read
+        build(c, k0, n);
+        __syncthreads();
+      }
+      float* rw = reinterpret_cast<float*>(red) + 2 * (wave * mc + li) + (g >> 1);
+      for (int tt = 0; tt < nt; tt += 2) {  // two trap tiles at a time
+        f32x4 tre[2], tim[2];
+        float2 q[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int t = min(tt + p, nt - 1);
+          tre[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+          tim[p] = tre[p];
+#pragma unroll
+          for (int ct = 0; ct < 2; ++ct) {
+            const unsigned* xb = xf + (t * CT + 2 * part + ct) * kFragWords + ewofs;
+            u32x4 xh, xl;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              xh[v] = xb[4 * v];
+              xl[v] = xb[4 * v + kLoWords];
+            }
+            tre[p] = mfma32(eh[ct], xh, tre[p]);
+            tim[p] = mfma32(fh[ct], xh, tim[p]);
+            tre[p] = mfma32(el[ct], xh, tre[p]);
+            tim[p] = mfma32(fl[ct], xh, tim[p]);
+            tre[p] = mfma32(eh[ct], xl, tre[p]);
+            tim[p] = mfma32(fh[ct], xl, tim[p]);
+          }
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int m = 16 * min(tt + p, nt - 1) + li;
+          const float2 k = rk[rt * mc + m];
+          const float qf = qv[m];
+          float2 y[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float t = __builtin_fmaf(qf, fq[v], __builtin_fmaf(k.y, fi[v], k.x));
+            y[v] = make_float2(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+          }
+          q[p] = fold_rows(y, tre[p], tim[p]);
+        }
+        const float v = sum_groups(q[0], q[1]);
+        if (tt + (g & 1) < nt) rw[32 * (tt + (g & 1))] = v;
+      }
+      __syncthreads();
+      for (int m = threadIdx.x; m < n && k0 + m < M; m += NT) {
+        float2 acc = red[m];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
           acc.x += red[w * mc + m].x;
           acc.y += red[w * mc + m].y;
         }
@@ -580,6 +956,37 @@ hipError_t tile_mode(hipStream_t s, const SepArgs& a) {
   }
 }
 
+template <int MODE, int OCC>
+hipError_t wide_t(hipStream_t s, const SepArgs& a) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_wide<MODE, OCC>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax);
+  if (attr != hipSuccess) return attr;
+  const size_t lds = wide_lds_bytes(a.sc, a.mmax);
+  if (lds > (size_t)kLdsMax || a.sc > kWideTraps) return hipErrorInvalidValue;
+  if (MODE == 0 && (!a.acc_in || !a.acc_out || !a.acc_zero || a.T < 1)) return hipErrorInvalidValue;
+  constexpr TileShape sh = kTileShapes[kTileWide];
+  dim3 grid(sh.gx(a.nx), sh.gy(a.ny), a.B);
+  hipLaunchKernelGGL((k_wide<MODE, OCC>), grid, dim3(512), lds, s, a.coef, a.st_in, a.acc_in, a.B == 1 ? a.one_m : 0,
+                     a.B == 1 ? a.one_off : 0, a.T, a.acc_unscale, a.nx, a.ny, a.sc, a.upd, a.hd, a.st_out, a.vin,
+                     a.hist, a.flag, a.inv_n, a.phase, a.grad, a.partial, a.acc_out, a.acc_zero, a.acc_scale);
+  return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t wide_occ(hipStream_t s, const SepArgs& a) {
+  return a.occ == 2 ? wide_t<MODE, 2>(s, a) : wide_t<MODE, 1>(s, a);
+}
+
+hipError_t wide_mode(hipStream_t s, const SepArgs& a) {
+  switch (a.mode) {
+    case 0: return wide_occ<0>(s, a);
+    case 1: return wide_occ<1>(s, a);
+    case 2: return wide_occ<2>(s, a);
+    case 3: return wide_occ<3>(s, a);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 // Figures of merit of `n` consecutive masks of a solve from their V (hist [slot][T]): block (slot, b)
 // writes stats[b][k0 + slot].
 __global__ void __launch_bounds__(256)
@@ -606,7 +1013,7 @@ hipError_t launch_tile(hipStream_t s, const SepArgs& a) {
   switch (a.shape) {
     case kTile32: return tile_mode<2, 2, 1, 1>(s, a);
     case kTile32Split: return tile_mode<2, 2, 1, 2>(s, a);
-    case kTile64: return tile_mode<4, 2, 2, 1>(s, a);
+    case kTileWide: return wide_mode(s, a);
     default: return hipErrorInvalidValue;
   }
 }

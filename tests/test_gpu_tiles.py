@@ -26,9 +26,10 @@ def _announce(request):
 
 
 # (nx, ny, traps): 32 x 32 blocks with 4 or 8 waves, 64 x 64 blocks (grids of half as many as the
-# compute units), one and several trap tiles and super-chunks, grids off every multiple
+# compute units; of more than the compute units, two to a unit), one and several trap tiles and
+# super-chunks, grids off every multiple
 EDGES = [(16, 16, 1), (17, 33, 15), (31, 65, 16), (64, 32, 17), (33, 100, 48), (96, 65, 49), (127, 129, 65),
-         (700, 840, 5), (705, 769, 40), (769, 705, 97)]
+         (700, 840, 5), (705, 769, 40), (769, 705, 97), (700, 840, 257), (1030, 1100, 17), (1030, 1100, 120)]
 
 
 @pytest.mark.parametrize("nx,ny,m", EDGES)
@@ -51,7 +52,8 @@ def relative(x, ref):
 
 
 @pytest.mark.parametrize("nx,ny,counts", [(16, 16, [1, 16]), (33, 31, [17, 3, 33]), (130, 65, [300, 2]),
-                                          (512, 257, [64, 5, 100, 31, 48, 16]), (200, 72, [2048])])
+                                          (512, 257, [64, 5, 100, 31, 48, 16]), (200, 72, [2048]),
+                                          (641, 833, [273]), (545, 577, [7, 130, 64, 1])])
 def test_fields_and_gradients_at_edges(hot, nx, ny, counts):
     rng = np.random.default_rng(7 * nx + ny)
     slm, T = W.Slm(nx, ny), int(sum(counts))
