@@ -60,6 +60,13 @@ constexpr int kGraphCache = 128;
 // masks whose V is kept before their figures of merit are taken, and the memory that may take
 constexpr int kHistMasks = 64;
 constexpr int64_t kHistBytes = int64_t(64) << 20;
+// Solves of at most this many iterations are launched eagerly: starting a replay costs about 5 us more
+// than the same launches one by one, which the host gives out faster (2-3 us each) than the device
+// works them off (4 us and more).  Per solve, eagerly against by replay: random superposition 128 x 96
+// x 10 traps 22 against 48 us; GSW 256^2 x 16 with 3 / 10 / 20 iterations 27 / 59 / 101 against 33 /
+// 63 / 107 us, 512^2 x 100 39 / 88 / 158 against 44 / 94 / 164 us.  Longer sequences keep the host free
+// with one replay, for 1-2 %.
+constexpr int kEagerIters = 24;
 constexpr double kPi = 3.14159265358979323846;
 
 }  // namespace
@@ -89,7 +96,12 @@ struct hot_ctx {
   DevBuf acc;  // fused paths: 3 rotating buffers of fixed-point trap sums [kAccRegions][T] u64 (re + 2^32 im)
   Staging ring[kRing];
   int ring_pos = 0;
-  int* flag_host = nullptr;  // pinned
+  int* flag_host = nullptr;  // pinned, and the same as the device addresses it
+  int* flag_host_dev = nullptr;
+  // tile kernels: statistics of a call that asks for them, written by the device
+  float* hstats = nullptr;
+  float* hstats_dev = nullptr;
+  size_t hstats_cap = 0;
   // allocation-free entry point: the device address of this GPU's fixed workspace, and a pinned
   // host buffer of the same size (its device mapping, and an event behind its last upload), all
   // set up by hot_create
@@ -132,15 +144,12 @@ int ensure(hot_ctx* c, DevBuf& b, size_t bytes) {
   return HOT_OK;
 }
 
-// Asynchronous host-to-device copy through a ring of pinned staging buffers, so the
-// caller's host arrays may be reused as soon as the call returns.  The copy is a kernel on the
-// context's stream that reads the pinned buffer through its device mapping (the runtime's own
-// copy of a few hundred bytes was measured to stall the stream for ~0.5 ms after some launch
-// sequences); a slot is reused only after the event behind its copy has completed.  Sizes are
-// multiples of 16 bytes (the tables are arrays of 16- and 32-byte records).
-int upload(hot_ctx* c, void* dst, const void* src, size_t bytes) {
-  if (bytes == 0) return HOT_OK;
-  if (bytes % 16 != 0) return fail(HOT_EINVAL, "internal: upload of %zu bytes is not a multiple of 16", bytes);
+// The next slot of a ring of pinned staging buffers, with room for `bytes`: the caller's host arrays are
+// copied there and may be reused as soon as the call returns.  The device reads the slot through its
+// device mapping in a kernel on the context's stream (the runtime's own copy of a few hundred bytes was
+// measured to stall the stream for ~0.5 ms after some launch sequences); a slot is reused only after the
+// event behind that kernel has completed.
+int stage_slot(hot_ctx* c, size_t bytes, Staging** out) {
   Staging& s = c->ring[c->ring_pos];
   c->ring_pos = (c->ring_pos + 1) % kRing;
   if (s.pending) {
@@ -156,6 +165,7 @@ int upload(hot_ctx* c, void* dst, const void* src, size_t bytes) {
     hipError_t e = hipHostMalloc(&s.host, want, hipHostMallocDefault);
     if (e != hipSuccess) {
       (void)hipGetLastError();
+      s.host = nullptr;
       return fail(HOT_ENOMEM, "pinned host allocation of %zu bytes failed", want);
     }
     e = hipHostGetDevicePointer(&s.dev, s.host, 0);
@@ -168,10 +178,25 @@ int upload(hot_ctx* c, void* dst, const void* src, size_t bytes) {
     }
     s.cap = want;
   }
-  memcpy(s.host, src, bytes);
-  HIP_TRY(launch_copy16(c->stream, s.dev, dst, bytes / 16));
-  HIP_TRY(hipEventRecord(s.ev, c->stream));
-  s.pending = true;
+  *out = &s;
+  return HOT_OK;
+}
+
+// Pinned host memory for the statistics of a call that synchronises (the device writes them there).
+int ensure_host_stats(hot_ctx* c, size_t bytes) {
+  if (bytes <= c->hstats_cap) return HOT_OK;
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  if (c->hstats) HIP_TRY(hipHostFree(c->hstats));
+  c->hstats = nullptr;
+  c->hstats_cap = 0;
+  const size_t want = std::max<size_t>(bytes, 4096);
+  if (hipHostMalloc((void**)&c->hstats, want, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    c->hstats = nullptr;
+    return fail(HOT_ENOMEM, "pinned host allocation of %zu bytes failed", want);
+  }
+  HIP_TRY(hipHostGetDevicePointer((void**)&c->hstats_dev, c->hstats, 0));
+  c->hstats_cap = want;
   return HOT_OK;
 }
 
@@ -518,9 +543,11 @@ int prepare(hot_ctx* c, int variant, const hot_slm* slm, int B, const int32_t* c
 }
 
 // Device tables: coef [T], hd [2B] (fused-kernel layouts, then stand-alone trap-pass
-// layouts), state [2T] (double buffer: iteration k reads one half and writes the other).
+// layouts), state [2T] (double buffer: iteration k reads one half and writes the other).  One launch
+// writes what is new of them, takes the weights from w0 (device) when given, and clears the buffer of
+// fixed-point sums `zero` when given.
 int upload_tables(hot_ctx* c, const hot_slm* slm, const Plan& P, const double* xyz, const int32_t* counts,
-                  bool with_state = true) {
+                  bool with_state = true, const float* w0 = nullptr, unsigned long long* zero = nullptr) {
   std::vector<double> key;
   key.reserve(10 + P.B + 3 * (size_t)P.T);
   key.push_back(slm->nx);
@@ -539,15 +566,45 @@ int upload_tables(hot_ctx* c, const hot_slm* slm, const Plan& P, const double* x
   key.insert(key.end(), xyz, xyz + 3 * (size_t)P.T);
   int rc;
   if ((rc = ensure(c, c->st, 2 * sizeof(TrapState) * P.T))) return rc;
-  if (with_state && (rc = upload(c, c->st.p, c->h_st.data(), sizeof(TrapState) * P.T))) return rc;
-  if (key == c->key && c->coef.p && c->hd.p) return HOT_OK;
-  c->key.clear();
-  c->amat_valid = false;
-  if ((rc = ensure(c, c->coef, sizeof(TrapCoef) * P.T))) return rc;
-  if ((rc = ensure(c, c->hd, sizeof(HoloDesc) * 2 * P.B))) return rc;
-  if ((rc = upload(c, c->coef.p, c->h_coef.data(), sizeof(TrapCoef) * P.T))) return rc;
-  if ((rc = upload(c, c->hd.p, c->h_hd.data(), sizeof(HoloDesc) * 2 * P.B))) return rc;
-  c->key.swap(key);
+  const bool fresh = !(key == c->key && c->coef.p && c->hd.p);
+  if (fresh) {
+    c->key.clear();
+    c->amat_valid = false;
+    if ((rc = ensure(c, c->coef, sizeof(TrapCoef) * P.T))) return rc;
+    if ((rc = ensure(c, c->hd, sizeof(HoloDesc) * 2 * P.B))) return rc;
+  }
+  if (!fresh && !with_state && !zero) return HOT_OK;
+  const size_t nst = with_state ? sizeof(TrapState) * P.T : 0, nco = fresh ? sizeof(TrapCoef) * P.T : 0,
+               nhd = fresh ? sizeof(HoloDesc) * 2 * P.B : 0;
+  Staging* s = nullptr;
+  if ((rc = stage_slot(c, nst + nco + nhd, &s))) return rc;
+  if (nst) memcpy(s->host, c->h_st.data(), nst);
+  if (nco) memcpy((char*)s->host + nst, c->h_coef.data(), nco);
+  if (nhd) memcpy((char*)s->host + nst + nco, c->h_hd.data(), nhd);
+  UploadArgs u;
+  const size_t at[3] = {0, nst, nst + nco}, bytes[3] = {nst, nco, nhd};
+  void* to[3] = {c->st.p, c->coef.p, c->hd.p};
+  for (int i = 0; i < 3; ++i) {
+    u.src[i] = (const uint4*)((const char*)s->dev + at[i]);
+    u.dst[i] = (uint4*)to[i];
+    u.n[i] = (unsigned)(bytes[i] / 16);
+  }
+  u.w0 = w0;
+  u.zero = (uint4*)zero;
+  u.nzero = zero ? (unsigned)(sizeof(uint64_t) * kAccRegions * P.T / 16) : 0;
+  HIP_TRY(launch_upload(c->stream, u));
+  HIP_TRY(hipEventRecord(s->ev, c->stream));
+  s->pending = true;
+  if (fresh) c->key.swap(key);
+  return HOT_OK;
+}
+
+// The host copy of the degenerate flag, as the stream left it: reported, and the flag cleared.
+int report_flag(hot_ctx* c) {
+  if (*c->flag_host) {
+    HIP_TRY(launch_fill_u32(c->stream, (unsigned*)c->flag.p, 0u, 1));
+    return fail(HOT_EDEGENERATE, "GSW/GS met <|V|> = 0: the phase mask sends no light to any trap");
+  }
   return HOT_OK;
 }
 
@@ -555,11 +612,7 @@ int upload_tables(hot_ctx* c, const hot_slm* slm, const Plan& P, const double* x
 int take_flag(hot_ctx* c) {
   HIP_TRY(hipMemcpyAsync(c->flag_host, c->flag.p, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
-  if (*c->flag_host) {
-    HIP_TRY(launch_fill_u32(c->stream, (unsigned*)c->flag.p, 0u, 1));
-    return fail(HOT_EDEGENERATE, "GSW/GS met <|V|> = 0: the phase mask sends no light to any trap");
-  }
-  return HOT_OK;
+  return report_flag(c);
 }
 
 enum Algo { kRS = 0, kGS = 1, kGSW = 2 };
@@ -652,21 +705,33 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   const bool separable = variant == HOT_SEPARABLE;
   const bool tiles = P.tiles;
   const int nblk = stored ? P.nblk_stored : separable ? P.nblk_sep : P.fg.nblk();
-  if ((rc = upload_tables(c, slm, P, xyz, counts))) return rc;
+  if (!stored && (rc = ensure_acc(c, P))) return rc;
+  if ((rc = upload_tables(c, slm, P, xyz, counts, true, w0, stored ? nullptr : acc_buf(c, P, 1)))) return rc;
   if (stored && (rc = ensure(c, c->partial, sizeof(float2) * (size_t)P.T * nblk))) return rc;
   if ((rc = ensure(c, c->stats, sizeof(float) * 3 * (size_t)B * (K + 1)))) return rc;
   if (stored && (rc = ensure_stored(c, P))) return rc;
-  if (!stored && (rc = ensure_acc(c, P))) return rc;
   // tile kernels: V of up to `ring` masks is kept, and their figures of merit taken together
   const int ring = (int)std::max<int64_t>(1, std::min<int64_t>({K, kHistMasks, kHistBytes / (8 * (int64_t)P.T)}));
   const bool want = tiles && stats && K > 0;
   if (want && (rc = ensure(c, c->hist, sizeof(float2) * (size_t)ring * P.T))) return rc;
+  // and, when the caller asks for them, written to pinned host memory by the device (no copy)
+  const bool direct_stats = tiles && stats;
+  if (direct_stats && (rc = ensure_host_stats(c, sizeof(hot_stats) * (size_t)B * (K + 1)))) return rc;
   TrapState* st[2] = {(TrapState*)c->st.p, (TrapState*)c->st.p + P.T};
-  if (w0) HIP_TRY(launch_import_w(c->stream, w0, st[0], P.T));
 
   const HoloDesc* hd = (const HoloDesc*)c->hd.p;
   float2* part = (float2*)c->partial.p;
-  float* dstats = (float*)c->stats.p;
+  float* dstats = direct_stats ? c->hstats_dev : (float*)c->stats.p;
+  FinishArgs fin;
+  fin.B = B;
+  fin.T = P.T;
+  fin.unscale = P.acc_unscale;
+  fin.hd = hd;
+  fin.V = V;
+  fin.stats = dstats;
+  fin.stat_stride = K + 1;
+  fin.hist = (const float2*)c->hist.p;
+  fin.flag = (const int*)c->flag.p;
   const float inv_n = (float)(1.0 / (double)P.n);
   const int upd = algo == kGSW ? 2 : 1;
 
@@ -676,7 +741,6 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
     if (separable || tiles) {
       // one launch per iteration, with the same rotation of fixed-point sums as the direct path
       SepArgs a = tiles ? tile_args(c, P, 0, phase, K) : sep_args(c, P, 0, phase, K);
-      e = launch_fill_u32(s, (unsigned*)acc_buf(c, P, 1), 0u, 2 * kAccRegions * P.T);
       for (int k = 0; k <= K && e == hipSuccess; ++k) {
         a.upd = k == 0 ? 0 : upd;
         a.st_in = k == 0 ? st[0] : st[(k - 1) & 1];
@@ -689,14 +753,19 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
         const int slot = k > 0 ? (k - 1) % ring : 0;
         if (want && k > 0) a.hist = (float2*)c->hist.p + (size_t)slot * P.T;
         e = tiles ? launch_tile(s, a) : launch_sep(s, a);
-        if (e == hipSuccess && want && k > 0 && (slot == ring - 1 || k == K))
-          e = launch_stats(s, slot + 1, B, P.T, (const float2*)c->hist.p, hd, st[0], dstats, k - 1 - slot, K + 1);
+        if (e == hipSuccess && want && k > 0 && slot == ring - 1 && k < K) {  // the ring is full
+          FinishArgs f = fin;
+          f.last = false;
+          f.st = st[0];
+          f.nhist = ring;
+          f.kstat = k;
+          e = launch_finish(s, f);
+        }
       }
     } else if (!stored) {
-      // one launch per iteration: launch k reads buffer k % 3, adds into (k + 1) % 3 (buffer 1 is
-      // cleared first, the others by the launches) and clears (k + 2) % 3
+      // one launch per iteration: launch k reads buffer k % 3, adds into (k + 1) % 3 (buffer 1 was
+      // cleared with the upload, the others are by the launches) and clears (k + 2) % 3
       IterArgs a = iter_args(c, P, phase, K);
-      e = launch_fill_u32(s, (unsigned*)acc_buf(c, P, 1), 0u, 2 * kAccRegions * P.T);
       for (int k = 0; k <= K && e == hipSuccess; ++k) {
         a.upd = k == 0 ? 0 : upd;
         a.st_in = k == 0 ? st[0] : st[(k - 1) & 1];
@@ -720,19 +789,28 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
         if (e == hipSuccess) e = launch_reduce(s, B, P.mmax, nblk, inv_n, part, hd, V);
       }
     }
-    // the final mask's V and figures of merit (fused paths: from the last buffer of sums)
-    if (e == hipSuccess)
-      e = stored ? launch_update(s, B, V, hd, st[K & 1], st[K & 1], dstats, K, K + 1, 0, (int*)c->flag.p)
-                 : launch_finish(s, B, P.T, acc_buf(c, P, (K + 1) % 3), P.acc_unscale, hd, st[K & 1], V, dstats, K,
-                                 K + 1);
-    if (e == hipSuccess && (w_out || theta_out)) e = launch_export_state(s, st[K & 1], P.T, w_out, theta_out);
+    // the final mask's V and figures of merit (fused paths: from the last buffer of sums), and the state
+    if (e == hipSuccess && stored)
+      e = launch_update(s, B, V, hd, st[K & 1], st[K & 1], dstats, K, K + 1, 0, (int*)c->flag.p);
+    if (e == hipSuccess) {
+      FinishArgs f = fin;
+      f.acc = stored ? nullptr : acc_buf(c, P, (K + 1) % 3);
+      f.st = st[K & 1];
+      f.kstat = K;
+      f.nhist = want ? (K - 1) % ring + 1 : 0;
+      f.w_out = w_out;
+      f.theta_out = theta_out;
+      f.flag_out = direct_stats ? c->flag_host_dev : nullptr;
+      if (!stored) e = launch_finish(s, f);
+      else if (w_out || theta_out) e = launch_export_state(s, st[K & 1], P.T, w_out, theta_out);
+    }
     return e;
   };
 
   // Replay a captured graph of the sequence when one with the same shapes and pointers
   // exists (captured on the context's own stream, launched on the caller's).
   bool done = false;
-  if (c->use_graphs) {
+  if (c->use_graphs && K > kEagerIters) {
     std::vector<uint64_t> key = {(uint64_t)B, (uint64_t)P.T, (uint64_t)P.nx, (uint64_t)P.ny, (uint64_t)K,
                                  (uint64_t)algo, (uint64_t)variant, (uint64_t)P.fract, (uint64_t)P.nt, (uint64_t)P.q,
                                  (uint64_t)P.tpl, (uint64_t)P.fg.seg_w, (uint64_t)P.sep_w, (uint64_t)P.sep_sc, (uint64_t)P.sep_kh,
@@ -740,7 +818,7 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
                                  (uint64_t)(uintptr_t)V, (uint64_t)(uintptr_t)w_out, (uint64_t)(uintptr_t)theta_out,
                                  (uint64_t)(uintptr_t)c->coef.p, (uint64_t)(uintptr_t)c->st.p,
                                  (uint64_t)(uintptr_t)c->hd.p, (uint64_t)(uintptr_t)c->partial.p,
-                                 (uint64_t)(uintptr_t)c->stats.p, (uint64_t)(uintptr_t)c->amat.p,
+                                 (uint64_t)(uintptr_t)dstats, (uint64_t)(uintptr_t)c->amat.p,
                                  (uint64_t)(uintptr_t)c->efield.p, (uint64_t)(uintptr_t)c->acc.p};
     hot_ctx::GraphEntry* hit = nullptr;
     for (auto& g : c->graphs)
@@ -777,6 +855,11 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
     }
   }
   if (!done) HIP_TRY(enqueue(c->stream));
+  if (direct_stats) {
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    memcpy(stats, c->hstats, sizeof(hot_stats) * (size_t)B * (K + 1));
+    return report_flag(c);
+  }
   if (stats) {
     HIP_TRY(hipMemcpyAsync(stats, dstats, sizeof(float) * 3 * (size_t)B * (K + 1), hipMemcpyDeviceToHost,
                            c->stream));
@@ -890,6 +973,8 @@ int hot_create(hot_ctx** out, int device, void* stream) {
     return bail(fail(HOT_EDEVICE, "pinned staging buffer has no device mapping"));
   if (hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) != hipSuccess)
     return bail(fail(HOT_EDEVICE, "event creation failed"));
+  if (hipHostGetDevicePointer((void**)&c->flag_host_dev, c->flag_host, 0) != hipSuccess || !c->flag_host_dev)
+    return bail(fail(HOT_EDEVICE, "pinned flag has no device mapping"));
   *c->flag_host = 0;
   int rc = ensure(c, c->flag, sizeof(int));
   if (rc) return bail(rc);
@@ -913,6 +998,7 @@ int hot_destroy(hot_ctx* c) {
     if (s.ev) (void)hipEventDestroy(s.ev);
   }
   if (c->flag_host) (void)hipHostFree(c->flag_host);
+  if (c->hstats) (void)hipHostFree(c->hstats);
   if (c->na_ev) {
     if (c->na_pending) (void)hipEventSynchronize(c->na_ev);
     (void)hipEventDestroy(c->na_ev);
@@ -1048,16 +1134,40 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   unsigned long long* acc = (unsigned long long*)(base + L.acc);
   auto acc_of = [&](int i) { return acc + (size_t)i * kAccRegions * M; };
   int* flag = (int*)(base + L.flag);
-  float* dstats = (float*)(base + L.stats);
+  // statistics and flag go through the pinned staging buffer (its own regions, not the tables'): the
+  // tile kernels' last launch writes them there, the others' are copied
+  const bool direct_stats = P.tiles && stats;
+  float* dstats = (float*)((direct_stats ? c->na_dev : base) + L.stats);
   const int K = iters;
-  // tables in (coefficients, state, descriptors: one copy from the staging buffer's device
-  // mapping), then the launch sequence of hot_gsw, eagerly, with every buffer in the workspace
-  HIP_TRY(launch_copy16(c->stream, c->na_dev + L.coef, base + L.coef, (L.acc - L.coef) / 16));
+  FinishArgs fin;
+  fin.T = M;
+  fin.unscale = P.acc_unscale;
+  fin.hd = (const HoloDesc*)(base + L.hd);
+  fin.V = V;
+  fin.stats = dstats;
+  fin.stat_stride = K + 1;
+  fin.flag = flag;
+  fin.kstat = K;
+  // tables in (state, coefficients, descriptors, from the staging buffer's device mapping), with the
+  // words that must start at zero; then the launch sequence of hot_gsw, eagerly, with every buffer in
+  // the workspace
+  {
+    UploadArgs u;
+    const size_t at[3] = {L.st, L.coef, L.hd};
+    const size_t bytes[3] = {sizeof(TrapState) * (size_t)M, sizeof(TrapCoef) * (size_t)M, 2 * sizeof(HoloDesc)};
+    for (int i = 0; i < 3; ++i) {
+      u.src[i] = (const uint4*)(c->na_dev + at[i]);
+      u.dst[i] = (uint4*)(base + at[i]);
+      u.n[i] = (unsigned)(bytes[i] / 16);
+    }
+    u.w0 = w0;
+    u.zero = (uint4*)acc_of(1);
+    u.nzero = (unsigned)(sizeof(uint64_t) * kAccRegions * M / 16);
+    u.flag0 = (unsigned*)flag;
+    HIP_TRY(launch_upload(c->stream, u));
+  }
   HIP_TRY(hipEventRecord(c->na_ev, c->stream));
   c->na_pending = true;
-  HIP_TRY(launch_fill_u32(c->stream, (unsigned*)acc_of(1), 0u, 2 * kAccRegions * M));
-  HIP_TRY(launch_fill_u32(c->stream, (unsigned*)flag, 0u, 1));
-  if (w0) HIP_TRY(launch_import_w(c->stream, w0, st[0], M));
   const HoloDesc* hd = (const HoloDesc*)(base + L.hd);
   if (P.tiles) {
     SepArgs a;
@@ -1079,6 +1189,8 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     // V of the last masks, for their figures of merit: a ring behind the workspace
     float2* hist = (float2*)(base + kScratchBytes);
     const int ring = std::max(1, std::min({K, kHistMasks, (int)(kScratchHistBytes / (sizeof(float2) * (size_t)M))}));
+    fin.hist = hist;
+    fin.nhist = stats && K > 0 ? (K - 1) % ring + 1 : 0;
     for (int k = 0; k <= K; ++k) {
       a.upd = k == 0 ? 0 : kGSW;
       a.st_in = k == 0 ? st[0] : st[(k - 1) & 1];
@@ -1090,8 +1202,14 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
       const int slot = k > 0 ? (k - 1) % ring : 0;
       a.hist = stats && k > 0 ? hist + (size_t)slot * M : nullptr;
       HIP_TRY(launch_tile(c->stream, a));
-      if (stats && k > 0 && (slot == ring - 1 || k == K))
-        HIP_TRY(launch_stats(c->stream, slot + 1, 1, M, hist, hd, st[0], dstats, k - 1 - slot, K + 1));
+      if (stats && k > 0 && slot == ring - 1 && k < K) {  // the ring is full
+        FinishArgs f = fin;
+        f.last = false;
+        f.st = st[0];
+        f.nhist = ring;
+        f.kstat = k;
+        HIP_TRY(launch_finish(c->stream, f));
+      }
     }
   } else {
     IterArgs a;
@@ -1124,13 +1242,18 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
       HIP_TRY(launch_iter(c->stream, a));
     }
   }
-  HIP_TRY(launch_finish(c->stream, 1, M, acc_of((K + 1) % 3), P.acc_unscale, hd, st[K & 1], V, dstats, K, K + 1));
-  if (w_out || theta_out) HIP_TRY(launch_export_state(c->stream, st[K & 1], M, w_out, theta_out));
+  fin.acc = acc_of((K + 1) % 3);
+  fin.st = st[K & 1];
+  fin.w_out = w_out;
+  fin.theta_out = theta_out;
+  fin.flag_out = direct_stats ? (int*)(c->na_dev + L.flag) : nullptr;
+  HIP_TRY(launch_finish(c->stream, fin));
   if (stats) {
-    // statistics and flag through the pinned staging buffer (its own regions, not the tables')
-    HIP_TRY(hipMemcpyAsync(c->na_host + L.stats, dstats, 3 * sizeof(float) * ((size_t)K + 1), hipMemcpyDeviceToHost,
-                           c->stream));
-    HIP_TRY(hipMemcpyAsync(c->na_host + L.flag, flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    if (!direct_stats) {
+      HIP_TRY(hipMemcpyAsync(c->na_host + L.stats, dstats, 3 * sizeof(float) * ((size_t)K + 1), hipMemcpyDeviceToHost,
+                             c->stream));
+      HIP_TRY(hipMemcpyAsync(c->na_host + L.flag, flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    }
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->na_pending = false;
     memcpy(stats, c->na_host + L.stats, 3 * sizeof(float) * ((size_t)K + 1));

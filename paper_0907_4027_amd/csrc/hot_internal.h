@@ -126,11 +126,27 @@ hipError_t launch_iter(hipStream_t s, const IterArgs& a);
 
 // V (2T floats, interleaved) from one buffer of the direct path's fixed-point sums.
 hipError_t launch_collect(hipStream_t s, int T, const unsigned long long* acc, float unscale, float* V);
-// End of a solve: V from the sums and its figures of merit into stats[b][kstat] (st: the final
-// state, read but not changed), one block per hologram.
-hipError_t launch_finish(hipStream_t s, int B, int T, const unsigned long long* acc, float unscale,
-                         const HoloDesc* hd, const TrapState* st, float* V, float* stats, int kstat,
-                         int stat_stride);
+// End of a solve: V from the sums, its figures of merit into stats[b][kstat], the final state to w_out /
+// theta_out, and the figures of merit of the nhist masks before it from their kept V (without `last`
+// only these; kstat is then the mask after them).
+struct FinishArgs {
+  int B = 1, T = 0;
+  bool last = true;
+  const unsigned long long* acc = nullptr;
+  float unscale = 0.0f;
+  const HoloDesc* hd = nullptr;
+  const TrapState* st = nullptr;
+  float* V = nullptr;
+  float* stats = nullptr;
+  int kstat = 0, stat_stride = 1;
+  const float2* hist = nullptr;  // [nhist][T]
+  int nhist = 0;
+  float* w_out = nullptr;
+  float* theta_out = nullptr;
+  const int* flag = nullptr;
+  int* flag_out = nullptr;  // gets *flag when not null
+};
+hipError_t launch_finish(hipStream_t s, const FinishArgs& a);
 
 // Pixel pass alone (Eq. 3 with weights).  mode 0 writes the phase; mode 1 (adjoint) reads
 // `phase` and G (2T floats, interleaved) and writes grad[b][j] = (1/N) Im(e^{-i phi_j} sum_m G_m e^{i Delta_j^m}).
@@ -236,9 +252,6 @@ inline size_t wide_lds_bytes(int mc, int mmax) {
   return (size_t)(mc / 16) * 4 * 4 * kTileFragWords + 16384 + (size_t)mc * (4 * 8 + 4) + 8 * mp + 64;
 }
 hipError_t launch_tile(hipStream_t s, const SepArgs& a);
-// Figures of merit of n consecutive masks from their V (hist [n][T]) into stats[b][k0 ..].
-hipError_t launch_stats(hipStream_t s, int n, int B, int T, const float2* hist, const HoloDesc* hd,
-                        const TrapState* st, float* stats, int k0, int stat_stride);
 
 // Micro-benchmarks (hot_probes.hip): issue-rate probe of kind 0 (FMA), 1 (sin/cos) or 2 (the
 // direct passes' term: 4 FMA + sin + cos); every wave writes {shader clock, shader clock,
@@ -268,9 +281,20 @@ hipError_t scratch_address(int device, void** out);
 
 // Small helpers.
 hipError_t launch_fill_u32(hipStream_t s, unsigned* p, unsigned v, int n);
-// dst <- src, n16 16-byte words (src: device memory or the device mapping of pinned host memory).
-hipError_t launch_copy16(hipStream_t s, const void* src, void* dst, size_t n16);
+// w and theta of the state to w_out / theta_out (the stored variant).
 hipError_t launch_export_state(hipStream_t s, const TrapState* st, int t, float* w_out, float* theta_out);
-hipError_t launch_import_w(hipStream_t s, const float* w0, TrapState* st, int t);
+// The start of a call: tables from pinned host memory (its device mapping), n[i] 16-byte words each;
+// the first is the state, whose weights come from w0 (device) when not null; `zero` (nzero 16-byte
+// words) and *flag0 are cleared.
+struct UploadArgs {
+  const uint4* src[3] = {nullptr, nullptr, nullptr};
+  uint4* dst[3] = {nullptr, nullptr, nullptr};
+  unsigned n[3] = {0, 0, 0};
+  const float* w0 = nullptr;
+  uint4* zero = nullptr;
+  unsigned nzero = 0;
+  unsigned* flag0 = nullptr;
+};
+hipError_t launch_upload(hipStream_t s, const UploadArgs& a);
 
 }  // namespace hot

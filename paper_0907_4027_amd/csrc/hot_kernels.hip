@@ -606,23 +606,38 @@ k_collect(const unsigned long long* __restrict__ acc, int T, float unscale, floa
   V[2 * t + 1] = v.y;
 }
 
-// End of a solve on the fixed-point path, one block per hologram: V of its traps from the sums
-// (written to V) and their figures of merit into stats[b][kstat].
+// End of a solve on the fixed-point path.  Grid (nhist + 1, B): block (nhist, b) takes V of hologram b's
+// traps from the sums (written to V), their figures of merit into stats[b][kstat] and the final
+// weights and trap phases to w_out / theta_out (when not null); the blocks before it take the figures
+// of merit of the nhist masks before that from their kept V (hist [slot][T]) into stats[b][kstat - nhist
+// ..].  Without the last block in the grid (nhist, B) only the latter.  flag_out (when not null) gets
+// the degenerate flag.  One launch instead of three at the end of every solve: each costs its 2 us
+// however little it does.
 __global__ void __launch_bounds__(256)
 k_finish(const unsigned long long* __restrict__ acc, int T, float unscale, const HoloDesc* __restrict__ hd,
          const TrapState* __restrict__ st, float* __restrict__ V, float* __restrict__ stats, int kstat,
-         int stat_stride) {
+         int stat_stride, const float2* __restrict__ hist, int nhist, float* __restrict__ w_out,
+         float* __restrict__ theta_out, const int* __restrict__ flag, int* __restrict__ flag_out) {
   __shared__ float sh[8 * 4];
-  const int b = blockIdx.x;
+  const int b = blockIdx.y, slot = blockIdx.x;
   const int M = hd[b].m, off = hd[b].off;
+  auto none = [](int, const TrapState&) {};
+  float* row = stats + 3 * ((size_t)b * stat_stride + kstat - nhist + slot);
+  if (slot < nhist) {
+    const VArray v{reinterpret_cast<const float*>(hist + (size_t)slot * T), off};
+    update_traps<256>(v, st, off, M, 0, sh, row, nullptr, none);
+    return;
+  }
   const VAcc vacc{acc, T, off, unscale};
   for (int m = threadIdx.x; m < M; m += 256) {
     const float2 v = vacc(m);
     V[2 * (off + m)] = v.x;
     V[2 * (off + m) + 1] = v.y;
+    if (w_out) w_out[off + m] = st[off + m].w;
+    if (theta_out) theta_out[off + m] = st[off + m].theta_rad;
   }
-  update_traps<256>(vacc, st, off, M, 0, sh, stats + 3 * ((size_t)b * stat_stride + kstat), nullptr,
-                    [](int, const TrapState&) {});
+  if (flag_out && b == 0 && threadIdx.x == 0) *flag_out = *flag;
+  update_traps<256>(vacc, st, off, M, 0, sh, row, nullptr, none);
 }
 
 // One block per hologram: figures of merit of V into stats[b][kstat] and, for mode 1/2,
@@ -1307,12 +1322,6 @@ __global__ void __launch_bounds__(256) k_encode_u8(const float* __restrict__ pha
   }
 }
 
-// dst[i] = src[i] for n 16-byte words; src may be pinned host memory (read through its device
-// mapping), dst device memory.
-__global__ void __launch_bounds__(256) k_copy16(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
-}
-
 __global__ void k_fill_u32(unsigned* p, unsigned v, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -1326,9 +1335,25 @@ __global__ void k_export_state(const TrapState* __restrict__ st, int t, float* w
   }
 }
 
-__global__ void k_import_w(const float* __restrict__ w0, TrapState* __restrict__ st, int t) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < t) st[i].w = w0[i];
+// The start of a call in one launch: the trap tables from pinned host memory (read through its device
+// mapping) into place, the first of them the state, whose weights come from w0 when that is not null,
+// and the words that must start at zero.
+__global__ void __launch_bounds__(256) k_upload(UploadArgs a) {
+  const unsigned n01 = a.n[0] + a.n[1], n = n01 + a.n[2], step = gridDim.x * 256;
+  const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+  for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < n; i += step) {
+    if (i < a.n[0]) {
+      uint4 v = a.src[0][i];
+      if (a.w0) v.y = __builtin_bit_cast(unsigned, a.w0[i]);
+      a.dst[0][i] = v;
+    } else if (i < n01) {
+      a.dst[1][i - a.n[0]] = a.src[1][i - a.n[0]];
+    } else {
+      a.dst[2][i - n01] = a.src[2][i - n01];
+    }
+  }
+  for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < a.nzero; i += step) a.zero[i] = zero;
+  if (a.flag0 && blockIdx.x == 0 && threadIdx.x == 0) *a.flag0 = 0;
 }
 
 // ------------------------------------------------------------------ template dispatch
@@ -1464,11 +1489,11 @@ hipError_t launch_reduce(hipStream_t s, int B, int mmax, int nblk, float inv_n, 
   return hipGetLastError();
 }
 
-hipError_t launch_finish(hipStream_t s, int B, int T, const unsigned long long* acc, float unscale,
-                         const HoloDesc* hd, const TrapState* st, float* V, float* stats, int kstat,
-                         int stat_stride) {
-  hipLaunchKernelGGL(k_finish, dim3(B), dim3(256), 0, s, acc, T, unscale, hd, st, V, stats,
-                     kstat, stat_stride);
+hipError_t launch_finish(hipStream_t s, const FinishArgs& a) {
+  if (a.B < 1 || a.nhist + (a.last ? 1 : 0) < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_finish, dim3(a.nhist + (a.last ? 1 : 0), a.B), dim3(256), 0, s, a.acc, a.T, a.unscale, a.hd,
+                     a.st, a.V, a.stats, a.kstat, a.stat_stride, a.hist, a.nhist, a.w_out, a.theta_out, a.flag,
+                     a.flag_out);
   return hipGetLastError();
 }
 
@@ -1598,13 +1623,6 @@ hipError_t launch_encode_u8(hipStream_t s, const float* phase, uint8_t* frame, i
   return hipGetLastError();
 }
 
-hipError_t launch_copy16(hipStream_t s, const void* src, void* dst, size_t n16) {
-  if (n16 == 0) return hipSuccess;
-  const size_t blocks = std::min<size_t>((n16 + 255) / 256, 1024);
-  hipLaunchKernelGGL(k_copy16, dim3((unsigned)blocks), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, n16);
-  return hipGetLastError();
-}
-
 hipError_t launch_fill_u32(hipStream_t s, unsigned* p, unsigned v, int n) {
   hipLaunchKernelGGL(k_fill_u32, dim3((n + 255) / 256), dim3(256), 0, s, p, v, n);
   return hipGetLastError();
@@ -1615,8 +1633,11 @@ hipError_t launch_export_state(hipStream_t s, const TrapState* st, int t, float*
   return hipGetLastError();
 }
 
-hipError_t launch_import_w(hipStream_t s, const float* w0, TrapState* st, int t) {
-  hipLaunchKernelGGL(k_import_w, dim3((t + 255) / 256), dim3(256), 0, s, w0, st, t);
+hipError_t launch_upload(hipStream_t s, const UploadArgs& a) {
+  const unsigned words = std::max(a.n[0] + a.n[1] + a.n[2], a.nzero);
+  if (words == 0 && !a.flag0) return hipSuccess;
+  const unsigned blocks = std::min(std::max((words + 255) / 256, 1u), 1024u);
+  hipLaunchKernelGGL(k_upload, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -214,7 +214,7 @@ struct TrapInputs {
 //   fixed-point sums acc_in; 0: st_in as is), pixel pass, trap pass; the phase is written when not null.
 //   Each trap's block sum is added to acc_out's region of the wave's XCD, block (0, 0, b) writes
 //   hologram b's new state and clears its part of acc_zero, as in k_iter.  The figures of merit are not
-//   taken here: that block leaves V in `hist` (when not null) and k_stats works on several masks at a
+//   taken here: that block leaves V in `hist` (when not null) and k_finish works on several masks at a
 //   time (computed by one block before its pixel pass they held back the whole launch: 512^2 x 100 9.5
 //   against 8.7 us).
 // MODE 1: trap pass alone from the given phase (Eq. 1): per-block partials
@@ -987,25 +987,7 @@ hipError_t wide_mode(hipStream_t s, const SepArgs& a) {
   }
 }
 
-// Figures of merit of `n` consecutive masks of a solve from their V (hist [slot][T]): block (slot, b)
-// writes stats[b][k0 + slot].
-__global__ void __launch_bounds__(256)
-k_stats(const float2* __restrict__ hist, int T, const HoloDesc* __restrict__ hd, const TrapState* __restrict__ st,
-        float* __restrict__ stats, int k0, int stat_stride) {
-  __shared__ float sh[8 * 4];
-  const int b = blockIdx.y, slot = blockIdx.x;
-  const VArray v{reinterpret_cast<const float*>(hist + (size_t)slot * T), hd[b].off};
-  update_traps<256>(v, st, hd[b].off, hd[b].m, 0, sh, stats + 3 * ((size_t)b * stat_stride + k0 + slot), nullptr,
-                    [](int, const TrapState&) {});
-}
-
 }  // namespace
-
-hipError_t launch_stats(hipStream_t s, int n, int B, int T, const float2* hist, const HoloDesc* hd,
-                        const TrapState* st, float* stats, int k0, int stat_stride) {
-  hipLaunchKernelGGL(k_stats, dim3(n, B), dim3(256), 0, s, hist, T, hd, st, stats, k0, stat_stride);
-  return hipGetLastError();
-}
 
 hipError_t launch_tile(hipStream_t s, const SepArgs& a) {
   if (a.nx < 1 || a.ny < 1 || a.mmax < 1 || a.mmax > kMaxTraps || a.sc < 16 || a.sc % 16 != 0)

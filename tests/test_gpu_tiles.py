@@ -133,3 +133,27 @@ def test_changing_kernels_on_one_context(hot):
     for r in (a, b):
         assert_phase(to_np(r.phase), o["phi"])
         assert_V(to_np(r.V), o["V"])
+
+
+@pytest.mark.parametrize("nx,ny,m", [(150, 90, 24), (700, 840, 20)])
+def test_replays_of_long_solves_match_eager(hot, nx, ny, m):
+    """Long solves replay a captured graph: every replay, with other work and synchronisations between
+    them, gives the bits of the eager launches."""
+    p = W.random_problem(944, nx, ny, m)
+    q = W.random_problem(945, 96, 64, 7)
+    with hot.Context(0) as eager, hot.Context(0) as c:
+        eager.set_graphs(False)
+        ref = eager.hot_gsw(p.slm, p.xyz, p.theta0, 30, state=True)
+        torch.cuda.synchronize()
+        bufs = dict(phase=torch.empty(ny, nx, device="cuda"), V=torch.empty(m, 2, device="cuda"),
+                    w_out=torch.empty(m, device="cuda"), theta_out=torch.empty(m, device="cuda"))
+        for rep in range(4):
+            for b in bufs.values():
+                b.zero_()
+            r = c.hot_gsw(p.slm, p.xyz, p.theta0, 30, state=True, **bufs)
+            assert torch.equal(r.phase, ref.phase) and torch.equal(r.V, ref.V), rep
+            assert torch.equal(r.w, ref.w) and torch.equal(r.theta, ref.theta), rep
+            np.testing.assert_array_equal(r.stats, ref.stats)
+            if rep % 2:
+                c.hot_gsw(q.slm, q.xyz, q.theta0, 2)  # another problem on the same buffers of the context
+                torch.cuda.synchronize()
