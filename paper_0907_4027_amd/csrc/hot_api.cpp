@@ -93,7 +93,7 @@ struct hot_ctx {
   DevBuf probe;  // micro-benchmark sink and clock stamps
   DevBuf hist;   // tile kernels: V of the last masks of a solve, for their figures of merit
   DevBuf abl;    // per-block records of the pixel-pass ablation
-  DevBuf acc;  // fused paths: 3 rotating buffers of fixed-point trap sums [kAccRegions][T] u64 (re + 2^32 im)
+  DevBuf acc;  // fused paths: 3 rotating buffers of fixed-point trap sums [kAccRegions][acc_stride(T)] u64 (re + 2^32 im)
   Staging ring[kRing];
   int ring_pos = 0;
   int* flag_host = nullptr;  // pinned, and the same as the device addresses it
@@ -591,7 +591,7 @@ int upload_tables(hot_ctx* c, const hot_slm* slm, const Plan& P, const double* x
   }
   u.w0 = w0;
   u.zero = (uint4*)zero;
-  u.nzero = zero ? (unsigned)(sizeof(uint64_t) * kAccRegions * P.T / 16) : 0;
+  u.nzero = zero ? (unsigned)(sizeof(uint64_t) * kAccRegions * acc_stride(P.T) / 16) : 0;
   HIP_TRY(launch_upload(c->stream, u));
   HIP_TRY(hipEventRecord(s->ev, c->stream));
   s->pending = true;
@@ -649,7 +649,7 @@ SepArgs sep_args(hot_ctx* c, const Plan& P, int mode, float* phase, int K) {
   a.inv_n = (float)(1.0 / (double)P.n);
   a.phase = phase;
   a.partial = (float2*)c->partial.p;
-  a.T = P.T;
+  a.T = acc_stride(P.T);
   a.acc_scale = P.acc_scale;
   a.acc_unscale = P.acc_unscale;
   return a;
@@ -666,13 +666,15 @@ SepArgs tile_args(hot_ctx* c, const Plan& P, int mode, float* phase, int K) {
 
 // Buffer i (0..2) of the iteration kernels' rotating fixed-point sums.
 unsigned long long* acc_buf(hot_ctx* c, const Plan& P, int i) {
-  return (unsigned long long*)c->acc.p + (size_t)i * kAccRegions * P.T;
+  return (unsigned long long*)c->acc.p + (size_t)i * kAccRegions * acc_stride(P.T);
 }
-int ensure_acc(hot_ctx* c, const Plan& P) { return ensure(c, c->acc, 3 * sizeof(uint64_t) * kAccRegions * P.T); }
+int ensure_acc(hot_ctx* c, const Plan& P) {
+  return ensure(c, c->acc, 3 * sizeof(uint64_t) * kAccRegions * acc_stride(P.T));
+}
 
 IterArgs iter_args(hot_ctx* c, const Plan& P, float* phase, int K) {
   IterArgs a;
-  a.T = P.T;
+  a.T = acc_stride(P.T);
   a.acc_scale = P.acc_scale;
   a.acc_unscale = P.acc_unscale;
   a.fg = P.fg;
@@ -711,9 +713,9 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   if ((rc = ensure(c, c->stats, sizeof(float) * 3 * (size_t)B * (K + 1)))) return rc;
   if (stored && (rc = ensure_stored(c, P))) return rc;
   // tile kernels: V of up to `ring` masks is kept, and their figures of merit taken together
-  const int ring = (int)std::max<int64_t>(1, std::min<int64_t>({K, kHistMasks, kHistBytes / (8 * (int64_t)P.T)}));
+  const int ring = (int)std::max<int64_t>(1, std::min<int64_t>({K, kHistMasks, kHistBytes / (8 * (int64_t)acc_stride(P.T))}));
   const bool want = tiles && stats && K > 0;
-  if (want && (rc = ensure(c, c->hist, sizeof(float2) * (size_t)ring * P.T))) return rc;
+  if (want && (rc = ensure(c, c->hist, sizeof(float2) * (size_t)ring * acc_stride(P.T)))) return rc;
   // and, when the caller asks for them, written to pinned host memory by the device (no copy)
   const bool direct_stats = tiles && stats;
   if (direct_stats && (rc = ensure_host_stats(c, sizeof(hot_stats) * (size_t)B * (K + 1)))) return rc;
@@ -724,7 +726,7 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   float* dstats = direct_stats ? c->hstats_dev : (float*)c->stats.p;
   FinishArgs fin;
   fin.B = B;
-  fin.T = P.T;
+  fin.T = acc_stride(P.T);
   fin.unscale = P.acc_unscale;
   fin.hd = hd;
   fin.V = V;
@@ -751,7 +753,7 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
         a.kstat = k - 1;
         a.phase = k == K ? phase : nullptr;  // only the last mask's phase is returned
         const int slot = k > 0 ? (k - 1) % ring : 0;
-        if (want && k > 0) a.hist = (float2*)c->hist.p + (size_t)slot * P.T;
+        if (want && k > 0) a.hist = (float2*)c->hist.p + (size_t)slot * acc_stride(P.T);
         e = tiles ? launch_tile(s, a) : launch_sep(s, a);
         if (e == hipSuccess && want && k > 0 && slot == ring - 1 && k < K) {  // the ring is full
           FinishArgs f = fin;
@@ -888,10 +890,11 @@ int check_batch(const hot_slm* slm, int32_t B, const int32_t* M, const double* x
 
 // Layout of the allocation-free entry point's workspace for T traps and K iterations (byte
 // offsets, each region 256-byte aligned): coefficients [T], state [2][T], descriptors [2],
-// fixed-point trap sums [3][kAccRegions][T], statistics [K+1][3], the degenerate flag.  The
+// fixed-point trap sums [3][kAccRegions][acc_stride(T)], statistics [K+1][3], the degenerate flag.  The
 // pinned staging buffer uses the same offsets.
 struct NoallocLayout {
-  size_t coef, st, hd, acc, stats, flag, total;
+  size_t coef, st, hd, acc, stats, flag;
+  size_t total;  // without the rounding of acc_stride: what the limit is checked against
 };
 NoallocLayout noalloc_layout(int T, int K) {
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
@@ -904,12 +907,13 @@ NoallocLayout noalloc_layout(int T, int K) {
   L.hd = o;
   o = up(o + 2 * sizeof(HoloDesc));
   L.acc = o;
-  o = up(o + 3 * sizeof(uint64_t) * kAccRegions * (size_t)T);
+  o = up(o + 3 * sizeof(uint64_t) * kAccRegions * (size_t)acc_stride(T));
+  const size_t rounding = o - up(L.acc + 3 * sizeof(uint64_t) * kAccRegions * (size_t)T);
   L.stats = o;
   o = up(o + 3 * sizeof(float) * ((size_t)K + 1));
   L.flag = o;
   o = up(o + sizeof(int));
-  L.total = o;
+  L.total = o - rounding;
   return L;
 }
 
@@ -967,7 +971,7 @@ int hot_create(hot_ctx** out, int device, void* stream) {
   // same size and an event
   if (scratch_address(device, &c->scratch) != hipSuccess || !c->scratch)
     return bail(fail(HOT_EDEVICE, "the fixed device workspace has no address on device %d", device));
-  if (hipHostMalloc((void**)&c->na_host, kScratchBytes, hipHostMallocDefault) != hipSuccess)
+  if (hipHostMalloc((void**)&c->na_host, kScratchBytes + kScratchPad, hipHostMallocDefault) != hipSuccess)
     return bail(fail(HOT_ENOMEM, "pinned staging allocation failed"));
   if (hipHostGetDevicePointer((void**)&c->na_dev, c->na_host, 0) != hipSuccess || !c->na_dev)
     return bail(fail(HOT_EDEVICE, "pinned staging buffer has no device mapping"));
@@ -1132,7 +1136,8 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   char* base = (char*)c->scratch;
   TrapState* st[2] = {(TrapState*)(base + L.st), (TrapState*)(base + L.st) + M};
   unsigned long long* acc = (unsigned long long*)(base + L.acc);
-  auto acc_of = [&](int i) { return acc + (size_t)i * kAccRegions * M; };
+  const int ts = acc_stride(M);
+  auto acc_of = [&](int i) { return acc + (size_t)i * kAccRegions * ts; };
   int* flag = (int*)(base + L.flag);
   // statistics and flag go through the pinned staging buffer (its own regions, not the tables'): the
   // tile kernels' last launch writes them there, the others' are copied
@@ -1140,7 +1145,7 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   float* dstats = (float*)((direct_stats ? c->na_dev : base) + L.stats);
   const int K = iters;
   FinishArgs fin;
-  fin.T = M;
+  fin.T = ts;
   fin.unscale = P.acc_unscale;
   fin.hd = (const HoloDesc*)(base + L.hd);
   fin.V = V;
@@ -1162,7 +1167,7 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     }
     u.w0 = w0;
     u.zero = (uint4*)acc_of(1);
-    u.nzero = (unsigned)(sizeof(uint64_t) * kAccRegions * M / 16);
+    u.nzero = (unsigned)(sizeof(uint64_t) * kAccRegions * ts / 16);
     u.flag0 = (unsigned*)flag;
     HIP_TRY(launch_upload(c->stream, u));
   }
@@ -1183,12 +1188,12 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     a.coef = (const TrapCoef*)(base + L.coef);
     a.hd = hd;
     a.flag = flag;
-    a.T = M;
+    a.T = ts;
     a.acc_scale = P.acc_scale;
     a.acc_unscale = P.acc_unscale;
     // V of the last masks, for their figures of merit: a ring behind the workspace
-    float2* hist = (float2*)(base + kScratchBytes);
-    const int ring = std::max(1, std::min({K, kHistMasks, (int)(kScratchHistBytes / (sizeof(float2) * (size_t)M))}));
+    float2* hist = (float2*)(base + kScratchBytes + kScratchPad);
+    const int ring = std::max(1, std::min({K, kHistMasks, (int)(kScratchHistBytes / (sizeof(float2) * (size_t)ts))}));
     fin.hist = hist;
     fin.nhist = stats && K > 0 ? (K - 1) % ring + 1 : 0;
     for (int k = 0; k <= K; ++k) {
@@ -1200,7 +1205,7 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
       a.acc_zero = acc_of((k + 2) % 3);
       a.phase = k == K ? phase : nullptr;
       const int slot = k > 0 ? (k - 1) % ring : 0;
-      a.hist = stats && k > 0 ? hist + (size_t)slot * M : nullptr;
+      a.hist = stats && k > 0 ? hist + (size_t)slot * ts : nullptr;
       HIP_TRY(launch_tile(c->stream, a));
       if (stats && k > 0 && slot == ring - 1 && k < K) {  // the ring is full
         FinishArgs f = fin;
@@ -1224,7 +1229,7 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     a.fract = P.fract;
     a.coef = (const TrapCoef*)(base + L.coef);
     a.hd = (const HoloDesc*)(base + L.hd);
-    a.T = M;
+    a.T = ts;
     a.acc_scale = P.acc_scale;
     a.acc_unscale = P.acc_unscale;
     a.stats = dstats;
@@ -1417,13 +1422,13 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   // group 1: the reduction to V (per iteration on the stored path; once per solve, from the
   // fixed-point sums, on the fused paths)
   auto g1 = [&]() {
-    if (!stored) return launch_collect(c->stream, P.T, acc_buf(c, P, 0), P.acc_unscale, V);
+    if (!stored) return launch_collect(c->stream, P.T, acc_stride(P.T), acc_buf(c, P, 0), P.acc_unscale, V);
     return launch_reduce(c->stream, 1, P.mmax, P.nblk_stored, inv_n, part, hd, V);
   };
   // a fused path's buffer 0: sums of the theta0 mask (a pass without update)
   auto prime = [&]() -> hipError_t {
     if (stored) return hipSuccess;
-    hipError_t e = launch_fill_u32(c->stream, (unsigned*)acc_buf(c, P, 0), 0u, 2 * kAccRegions * P.T);
+    hipError_t e = launch_fill_u32(c->stream, (unsigned*)acc_buf(c, P, 0), 0u, 2 * kAccRegions * acc_stride(P.T));
     if (e != hipSuccess) return e;
     if (separable || tiles) {
       SepArgs p0 = sa;

@@ -141,7 +141,8 @@ struct VArray {
   int off;
   __device__ float2 operator()(int k) const { return make_float2(V[2 * (off + k)], V[2 * (off + k) + 1]); }
 };
-// ... or from the fixed-point sums of the fused kernels: kAccRegions regions of T 64-bit words.
+// ... or from the fixed-point sums of the fused kernels: kAccRegions regions, each T = acc_stride(traps)
+// 64-bit words from the next.
 // A block adds its sum (re, im) of a trap as one word, pack_sum: re and im are rounded to
 // integers in units of 1/scale, and the word is the 64-bit two's-complement value
 // re + 2^32 im.  Words add like integers, so a sum of words is R + 2^32 I with R, I the sums of

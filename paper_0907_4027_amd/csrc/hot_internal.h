@@ -95,6 +95,12 @@ struct FwdGeom {
 // [region][trap], one 64-bit word per trap (re and im packed, pack_sum in hot_kernels.hip); three
 // such buffers rotate over the iterations.
 constexpr int kAccRegions = 8;
+// Words from one region to the next: whole cache lines of 128 bytes, so that no line is added to by
+// two XCDs, whose L2s would take it from each other: GSW 512^2 x 100 took 9.2 us per launch with regions
+// of exactly T words, 8.9 with these (any T that is not a multiple of 16).  16 or 32 regions (each XCD's
+// blocks over two or four) shorten the queue of adds to a word further, but the next launch then waits
+// longer for V: 8.7 us here, and 256^2 x 16 180 -> 186 us a solve, 1024^2 x 256 746 -> 753.
+inline int acc_stride(int T) { return (T + 15) & ~15; }
 
 struct IterArgs {
   FwdGeom fg;
@@ -125,7 +131,7 @@ struct IterArgs {
 hipError_t launch_iter(hipStream_t s, const IterArgs& a);
 
 // V (2T floats, interleaved) from one buffer of the direct path's fixed-point sums.
-hipError_t launch_collect(hipStream_t s, int T, const unsigned long long* acc, float unscale, float* V);
+hipError_t launch_collect(hipStream_t s, int T, int stride, const unsigned long long* acc, float unscale, float* V);
 // End of a solve: V from the sums, its figures of merit into stats[b][kstat], the final state to w_out /
 // theta_out, and the figures of merit of the nhist masks before it from their kept V (without `last`
 // only these; kstat is then the mask after them).
@@ -276,6 +282,7 @@ hipError_t launch_encode_u8(hipStream_t s, const float* phase, uint8_t* frame, i
 // The fixed device workspace of the allocation-free entry point (hot_scratch.hip): its size, and
 // its device address on `device` (which must be the current device).
 constexpr size_t kScratchBytes = size_t(1) << 20;
+constexpr size_t kScratchPad = 4096;  // for the rounding of acc_stride, which the limit does not count
 constexpr size_t kScratchHistBytes = size_t(1) << 20;  // behind it: V of the last masks (tile kernels)
 hipError_t scratch_address(int device, void** out);
 

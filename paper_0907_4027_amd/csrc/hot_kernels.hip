@@ -598,10 +598,10 @@ k_reduce(const float2* __restrict__ partial, const HoloDesc* __restrict__ hd, in
 
 // V of all T traps from the fixed-point region sums of the direct path (one thread per trap).
 __global__ void __launch_bounds__(256)
-k_collect(const unsigned long long* __restrict__ acc, int T, float unscale, float* __restrict__ V) {
+k_collect(const unsigned long long* __restrict__ acc, int T, int stride, float unscale, float* __restrict__ V) {
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= T) return;
-  const float2 v = VAcc{acc, T, 0, unscale}(t);
+  const float2 v = VAcc{acc, stride, 0, unscale}(t);
   V[2 * t] = v.x;
   V[2 * t + 1] = v.y;
 }
@@ -609,7 +609,7 @@ k_collect(const unsigned long long* __restrict__ acc, int T, float unscale, floa
 // End of a solve on the fixed-point path.  Grid (nhist + 1, B): block (nhist, b) takes V of hologram b's
 // traps from the sums (written to V), their figures of merit into stats[b][kstat] and the final
 // weights and trap phases to w_out / theta_out (when not null); the blocks before it take the figures
-// of merit of the nhist masks before that from their kept V (hist [slot][T]) into stats[b][kstat - nhist
+// of merit of the nhist masks before that from their kept V (hist [slot][T], T = acc_stride(traps)) into stats[b][kstat - nhist
 // ..].  Without the last block in the grid (nhist, B) only the latter.  flag_out (when not null) gets
 // the degenerate flag.  One launch instead of three at the end of every solve: each costs its 2 us
 // however little it does.
@@ -1497,8 +1497,8 @@ hipError_t launch_finish(hipStream_t s, const FinishArgs& a) {
   return hipGetLastError();
 }
 
-hipError_t launch_collect(hipStream_t s, int T, const unsigned long long* acc, float unscale, float* V) {
-  hipLaunchKernelGGL(k_collect, dim3((T + 255) / 256), dim3(256), 0, s, acc, T, unscale, V);
+hipError_t launch_collect(hipStream_t s, int T, int stride, const unsigned long long* acc, float unscale, float* V) {
+  hipLaunchKernelGGL(k_collect, dim3((T + 255) / 256), dim3(256), 0, s, acc, T, stride, unscale, V);
   return hipGetLastError();
 }
 

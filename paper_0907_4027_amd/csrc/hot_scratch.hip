@@ -10,7 +10,7 @@ namespace hot {
 // statistics and the degenerate flag of one call, and behind them the trap fields of its last masks.  Every GPU the library runs on holds its own
 // copy until the process ends.  In host code `scratch` is only a stand-in for the symbol, never a
 // device address: the address comes from scratch_address().
-static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchHistBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchPad + kScratchHistBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
