@@ -124,7 +124,9 @@ enum hot_tuning_key {
                                    compute unit, else 512; 256 for the trap pass) */
   HOT_TUNE_SLICES = 4,          /* trap pass: at most this many pixel slices per wave, 1..16 */
   HOT_TUNE_GRAPHS = 5,          /* 1 (default): replay a captured hipGraph of a solve's launch
-                                   sequence when shapes and buffers repeat; 0: launch eagerly */
+                                   sequence when shapes and buffers repeat (solves of at most 24
+                                   iterations are launched eagerly: a replay costs about 5 us
+                                   more than their launches); 0: launch eagerly */
   HOT_TUNE_SEP_WAVES = 6,       /* separable variant: tiles of 16 x 16 pixels per block (1, 2 or 4),
                                    one or two waves each (HOT_TUNE_SEP_SPLIT) */
   HOT_TUNE_SEP_CHUNK = 7,       /* separable variant: traps whose tables a block holds in LDS at

@@ -609,9 +609,9 @@ k_collect(const unsigned long long* __restrict__ acc, int T, int stride, float u
 // End of a solve on the fixed-point path.  Grid (nhist + 1, B): block (nhist, b) takes V of hologram b's
 // traps from the sums (written to V), their figures of merit into stats[b][kstat] and the final
 // weights and trap phases to w_out / theta_out (when not null); the blocks before it take the figures
-// of merit of the nhist masks before that from their kept V (hist [slot][T], T = acc_stride(traps)) into stats[b][kstat - nhist
-// ..].  Without the last block in the grid (nhist, B) only the latter.  flag_out (when not null) gets
-// the degenerate flag.  One launch instead of three at the end of every solve: each costs its 2 us
+// of merit of the nhist masks before that from their kept V (hist [slot][T], T = acc_stride(traps)) into
+// stats[b][kstat - nhist ..].  Without the last block in the grid (nhist, B) only the latter.  flag_out
+// (when not null) gets the degenerate flag.  One launch instead of three at the end of every solve: each costs its 2 us
 // however little it does.
 __global__ void __launch_bounds__(256)
 k_finish(const unsigned long long* __restrict__ acc, int T, float unscale, const HoloDesc* __restrict__ hd,

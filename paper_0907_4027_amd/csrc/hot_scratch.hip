@@ -7,8 +7,8 @@
 namespace hot {
 
 // The workspace of hot_gsw_noalloc: the trap tables, the state, the fixed-point trap sums, the
-// statistics and the degenerate flag of one call, and behind them the trap fields of its last masks.  Every GPU the library runs on holds its own
-// copy until the process ends.  In host code `scratch` is only a stand-in for the symbol, never a
+// statistics and the degenerate flag of one call, and behind them the trap fields of its last masks.
+// Every GPU the library runs on holds its own copy until the process ends.  In host code `scratch` is only a stand-in for the symbol, never a
 // device address: the address comes from scratch_address().
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchPad + kScratchHistBytes];
 

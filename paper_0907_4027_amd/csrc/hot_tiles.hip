@@ -32,10 +32,10 @@
 //               lane groups are summed.
 //
 // What bounds it.  One iteration of 1024^2 x 256 is 8.6 GFLOP of products (5.1 us at the rate of the
-// halves) and 18.5 us per launch (k_wide), against 110 us of the direct sums; 512^2 x 100 takes 7.5 us
-// (15.9).  On the larger grid it is vector work beside the products (k_wide), on the smaller latency: 1.1 us from one launch to the next, 1.2 us until the first
-// coefficients are there, 1.2 us for the last trap sums to be added, and between them phases of a few
-// hundred instructions per wave at one or two waves per SIMD.
+// halves) and 17 to 19 us per launch (k_wide), against 108 us of the direct sums; 512^2 x 100 takes 6.9 us
+// (15.4).  On the larger grid it is vector work beside the products (k_wide), on the smaller latency: 1.2 us
+// from one launch to the next, 1.2 us until the first coefficients are there, 1 us more for V and the
+// update, and after them phases of a few hundred instructions per wave at two waves per SIMD.
 #include "hot_device.h"
 
 #include <algorithm>
@@ -117,6 +117,27 @@ __device__ __forceinline__ float sum_groups(float2 a, float2 b) {
 // and with 132 words per group of four traps both kinds of access reach every bank evenly.
 constexpr int kFragWords = kTileFragWords;
 constexpr int kTqWords = 132, kLoWords = 64;
+
+// A caller's phase in revolutions, reduced in FP64 to the nearest turn: as in the tables' constants, arguments
+// within half a turn of 0 round half as far as those of 0 .. 1.
+__device__ __forceinline__ float phase_turn(float ph) {
+  const double t = (double)ph * 0.15915494309189533577;  // 1 / (2 pi)
+  return (float)(t - __builtin_rint(t));
+}
+
+// e^{i 2pi t}.  EXACT: the library's sine and cosine instead of the hardware's (about 5e-8 rms off).  Eq. 1
+// by itself takes E and the column table with it: three factors carry three such errors where the direct
+// sum's term carries one, and V of 8 x 512^2 x 64 was 1.1e-7 off 64 bits (direct sums 9.9e-8); E alone gives
+// 7.7e-8, with the column table 5.3e-8, at no cost that can be measured (16.4 us a call either way).
+template <bool EXACT>
+__device__ __forceinline__ float2 unit_turn(float t) {
+  if constexpr (EXACT) {
+    float s, c;
+    sincospif(2.0f * t, &s, &c);
+    return make_float2(c, s);
+  }
+  return make_float2(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+}
 
 // E = S / |S|, 1 where S = 0 (arg 0 = 0), 0 outside the grid.  S is a sum of products of halves,
 // multiples of 2^-48, over weights scaled to at most 1: |S|^2 neither underflows nor overflows.
@@ -289,7 +310,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
     sl -= __builtin_rint(sl);
     double q = 4.0 * k.g;
     q -= __builtin_rint(q);
-    return make_float4((float)(kk - __builtin_floor(kk)), (float)sl, (float)q, 0.0f);
+    return make_float4((float)(kk - __builtin_rint(kk)), (float)sl, (float)q, 0.0f);
   };
   const double Xc = (double)(2 * (cb + 16 * tx + 8) - (nx - 1)), Yc = (double)(2 * (row0 + 16 * ty + 8) - (ny - 1));
   auto stage_refs = [&](int k0, int n) {
@@ -307,7 +328,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float t = __builtin_fmaf(k.z, fq[v], __builtin_fmaf(k.y, fi[v], k.x));
-      e[v] = make_float2(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+      e[v] = unit_turn<MODE == 1>(t);
     }
   };
   auto put_x = [&](int tt) {
@@ -478,7 +499,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
         for (int v = 0; v < 4; ++v) {
           if (inside(ct, v)) {
             const size_t px = pix0 + 16 * ct + v;
-            const float pr = caller_phase_rev(phase[px]);
+            const float pr = phase_turn(phase[px]);
             grad[px] = __builtin_amdgcn_ldexpf(
                 inv_n * (__builtin_amdgcn_cosf(pr) * sim[ct][v] - __builtin_amdgcn_sinf(pr) * sre[ct][v]), wexp);
           }
@@ -512,9 +533,9 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const bool in = inside(ct, v);
-        const float pr = in ? caller_phase_rev(phase[pix0 + 16 * ct + v]) : 0.0f;
-        er[v] = in ? __builtin_amdgcn_cosf(pr) : 0.0f;
-        ei[v] = in ? __builtin_amdgcn_sinf(pr) : 0.0f;
+        const float2 u = unit_turn<true>(in ? phase_turn(phase[pix0 + 16 * ct + v]) : 0.0f);
+        er[v] = in ? u.x : 0.0f;
+        ei[v] = in ? u.y : 0.0f;
       }
       put_e(ct, er, ei);
     }
@@ -538,21 +559,25 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
           const int t = min(tt + p, t1 - 1);
           tre[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
           tim[p] = tre[p];
+          u32x4 xh[CTW];
 #pragma unroll
           for (int ct = 0; ct < CTW; ++ct) {
             const unsigned* xb = xf + ((cwv * CTW + ct) * ntm + t) * kFragWords + ewofs;
-            u32x4 xh, xl;
+            u32x4 xl;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              xh[v] = xb[4 * v];
+              xh[ct][v] = xb[4 * v];
               xl[v] = xb[4 * v + kLoWords];
             }
-            tre[p] = mfma32(eh[ct], xh, tre[p]);
-            tim[p] = mfma32(fh[ct], xh, tim[p]);
-            tre[p] = mfma32(el[ct], xh, tre[p]);
-            tim[p] = mfma32(fl[ct], xh, tim[p]);
+            tre[p] = mfma32(el[ct], xh[ct], tre[p]);
+            tim[p] = mfma32(fl[ct], xh[ct], tim[p]);
             tre[p] = mfma32(eh[ct], xl, tre[p]);
             tim[p] = mfma32(fh[ct], xl, tim[p]);
+          }
+#pragma unroll
+          for (int ct = 0; ct < CTW; ++ct) {  // (the large products last: every sum before them rounds finer)
+            tre[p] = mfma32(eh[ct], xh[ct], tre[p]);
+            tim[p] = mfma32(fh[ct], xh[ct], tim[p]);
           }
         }
         float2 q[2];
@@ -667,7 +692,7 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
     sl -= __builtin_rint(sl);
     double q = 4.0 * c.q;
     q -= __builtin_rint(q);
-    const float2 ks = make_float2((float)(kk - __builtin_floor(kk)), (float)sl);
+    const float2 ks = make_float2((float)(kk - __builtin_rint(kk)), (float)sl);
     if (g & 1) {
       rk[rt * mc + m] = ks;
     } else {
@@ -687,7 +712,8 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float t = __builtin_fmaf(k.z, fq[v], __builtin_fmaf(k.y, fi[v], k.x));
-        const Split s = split(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+        const float2 u = unit_turn<MODE == 1>(t);
+        const Split s = split(u.x, u.y);
         x[4 * v] = s.hi;
         x[4 * v + kLoWords] = s.lo;
       }
@@ -813,7 +839,7 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
         for (int v = 0; v < 4; ++v) {
           if (inside(ct, v)) {
             const size_t px = pix0 + 16 * ct + v;
-            const float pr = caller_phase_rev(phase[px]);
+            const float pr = phase_turn(phase[px]);
             grad[px] = __builtin_amdgcn_ldexpf(
                 inv_n * (__builtin_amdgcn_cosf(pr) * sim[ct][v] - __builtin_amdgcn_sinf(pr) * sre[ct][v]), wexp);
           }
@@ -846,9 +872,9 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const bool in = inside(ct, v);
-        const float pr = in ? caller_phase_rev(phase[pix0 + 16 * ct + v]) : 0.0f;
-        er[v] = in ? __builtin_amdgcn_cosf(pr) : 0.0f;
-        ei[v] = in ? __builtin_amdgcn_sinf(pr) : 0.0f;
+        const float2 u = unit_turn<true>(in ? phase_turn(phase[pix0 + 16 * ct + v]) : 0.0f);
+        er[v] = in ? u.x : 0.0f;
+        ei[v] = in ? u.y : 0.0f;
       }
       put_e(ct, er, ei);
     }
@@ -876,21 +902,25 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
           const int t = min(tt + p, nt - 1);
           tre[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
           tim[p] = tre[p];
+          u32x4 xh[2];
 #pragma unroll
           for (int ct = 0; ct < 2; ++ct) {
             const unsigned* xb = xf + (t * CT + 2 * part + ct) * kFragWords + ewofs;
-            u32x4 xh, xl;
+            u32x4 xl;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              xh[v] = xb[4 * v];
+              xh[ct][v] = xb[4 * v];
               xl[v] = xb[4 * v + kLoWords];
             }
-            tre[p] = mfma32(eh[ct], xh, tre[p]);
-            tim[p] = mfma32(fh[ct], xh, tim[p]);
-            tre[p] = mfma32(el[ct], xh, tre[p]);
-            tim[p] = mfma32(fl[ct], xh, tim[p]);
+            tre[p] = mfma32(el[ct], xh[ct], tre[p]);
+            tim[p] = mfma32(fl[ct], xh[ct], tim[p]);
             tre[p] = mfma32(eh[ct], xl, tre[p]);
             tim[p] = mfma32(fh[ct], xl, tim[p]);
+          }
+#pragma unroll
+          for (int ct = 0; ct < 2; ++ct) {  // (the large products last: every sum before them rounds finer)
+            tre[p] = mfma32(eh[ct], xh[ct], tre[p]);
+            tim[p] = mfma32(fh[ct], xh[ct], tim[p]);
           }
         }
 #pragma unroll
