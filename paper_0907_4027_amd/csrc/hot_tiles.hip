@@ -125,18 +125,15 @@ __device__ __forceinline__ float phase_turn(float ph) {
   return (float)(t - __builtin_rint(t));
 }
 
-// e^{i 2pi t}.  EXACT: the library's sine and cosine instead of the hardware's (about 5e-8 rms off).  Eq. 1
-// by itself takes E and the column table with it: three factors carry three such errors where the direct
-// sum's term carries one, and V of 8 x 512^2 x 64 was 1.1e-7 off 64 bits (direct sums 9.9e-8); E alone gives
-// 7.7e-8, with the column table 5.3e-8, at no cost that can be measured (16.4 us a call either way).
-template <bool EXACT>
+// e^{i 2pi t} with the library's sine and cosine (the hardware's are about 5e-8 rms off).  Eq. 1 by itself
+// takes E with it: three factors carry three such errors where the direct sum's term carries one, and V of
+// 8 x 512^2 x 64 was 1.05e-7 off 64 bits (direct sums 9.9e-8); with E from here 7.7e-8.  The column table too
+// gives 5.3e-8, but costs 1.5 us of 5.9 (trap pass of 512^2 x 100) and 3.6 of 14.7 (1024^2 x 256); E costs
+// 0.5 of 10.6 us (8 x 512^2 x 64) and nothing that a call shows.
 __device__ __forceinline__ float2 unit_turn(float t) {
-  if constexpr (EXACT) {
-    float s, c;
-    sincospif(2.0f * t, &s, &c);
-    return make_float2(c, s);
-  }
-  return make_float2(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+  float s, c;
+  sincospif(2.0f * t, &s, &c);
+  return make_float2(c, s);
 }
 
 // E = S / |S|, 1 where S = 0 (arg 0 = 0), 0 outside the grid.  S is a sum of products of halves,
@@ -328,7 +325,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float t = __builtin_fmaf(k.z, fq[v], __builtin_fmaf(k.y, fi[v], k.x));
-      e[v] = unit_turn<MODE == 1>(t);
+      e[v] = make_float2(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
     }
   };
   auto put_x = [&](int tt) {
@@ -533,7 +530,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const bool in = inside(ct, v);
-        const float2 u = unit_turn<true>(in ? phase_turn(phase[pix0 + 16 * ct + v]) : 0.0f);
+        const float2 u = unit_turn(in ? phase_turn(phase[pix0 + 16 * ct + v]) : 0.0f);
         er[v] = in ? u.x : 0.0f;
         ei[v] = in ? u.y : 0.0f;
       }
@@ -712,8 +709,7 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float t = __builtin_fmaf(k.z, fq[v], __builtin_fmaf(k.y, fi[v], k.x));
-        const float2 u = unit_turn<MODE == 1>(t);
-        const Split s = split(u.x, u.y);
+        const Split s = split(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
         x[4 * v] = s.hi;
         x[4 * v + kLoWords] = s.lo;
       }
@@ -872,7 +868,7 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const bool in = inside(ct, v);
-        const float2 u = unit_turn<true>(in ? phase_turn(phase[pix0 + 16 * ct + v]) : 0.0f);
+        const float2 u = unit_turn(in ? phase_turn(phase[pix0 + 16 * ct + v]) : 0.0f);
         er[v] = in ? u.x : 0.0f;
         ei[v] = in ? u.y : 0.0f;
       }
