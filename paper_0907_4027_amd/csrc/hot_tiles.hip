@@ -15,7 +15,7 @@
 // rounding of an FP32 value just below 1, and a product is hi hi + hi lo + lo hi (the dropped lo lo is
 // below 2^-24): three half products for one FP32 product.  Measured against 64 bits over grids of 48 to
 // 2048 pixels a side and 3 to 1000 traps, fields and gradients are as close as with FP32 matrix products
-// (3.1e-7 against 3.3e-7 relative for the adjoint of 8 x 512^2 x 64) and closer than the direct sums
+// (2.3e-7 against 3.3e-7 relative for the adjoint of 8 x 512^2 x 64) and closer than the direct sums
 // (7.2e-7), whose per-term arguments reach several revolutions.  The weights are scaled by a power of two
 // so that the largest is below 1; all the rest (arguments, sine and cosine, normalisation, trap sums) is
 // FP32 or FP64 as in the other kernels.
