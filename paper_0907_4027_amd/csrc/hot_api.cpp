@@ -814,7 +814,10 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   // exists (captured on the context's own stream, launched on the caller's).
   bool done = false;
   if (c->use_graphs && K > kEagerIters) {
-    std::vector<uint64_t> key = {(uint64_t)B, (uint64_t)P.T, (uint64_t)P.nx, (uint64_t)P.ny, (uint64_t)K,
+    // everything a launch of the sequence is made of that may differ between calls: the largest trap
+    // count too, which sets the dynamic LDS and strides of a batch's launches (each hologram's own count
+    // is read on the device)
+    std::vector<uint64_t> key = {(uint64_t)B, (uint64_t)P.T, (uint64_t)P.mmax, (uint64_t)P.nx, (uint64_t)P.ny, (uint64_t)K,
                                  (uint64_t)algo, (uint64_t)variant, (uint64_t)P.fract, (uint64_t)P.nt, (uint64_t)P.q,
                                  (uint64_t)P.tpl, (uint64_t)P.fg.seg_w, (uint64_t)P.sep_w, (uint64_t)P.sep_sc, (uint64_t)P.sep_kh,
                                  (uint64_t)P.rows, (uint64_t)tiles, (uint64_t)want, (uint64_t)(uintptr_t)c->hist.p, (uint64_t)P.tile, (uint64_t)P.tile_occ, (uint64_t)P.tile_mc, (uint64_t)(uintptr_t)phase,
