@@ -178,7 +178,9 @@ int hot_gs(hot_ctx* ctx, const hot_slm* slm, int32_t M, const double* xyz, const
  *   w_out      device, M floats or NULL: the weights that produced the final phase
  *   theta_out  device, M floats or NULL: the trap phases that produced the final phase
  * Passing (theta_out, w_out) of a K1-iteration call back as (theta0, w0) and running K2
- * more iterations reproduces a single K1+K2 call bit for bit. */
+ * more iterations reproduces a single K1+K2 call bit for bit.
+ * A NaN weight makes every sum of Eq. 3 NaN, whose phase is taken as 0: the mask is flat and V its
+ * field.  An infinite weight makes the mask NaN and V 0 (HOT_EDEGENERATE once iterated). */
 int hot_gsw(hot_ctx* ctx, const hot_slm* slm, int32_t M, const double* xyz, const double* theta0,
             uint64_t seed, int32_t iters, const float* w0, float* w_out, float* theta_out,
             float* phase, float* V, hot_stats* stats);
@@ -221,7 +223,8 @@ int hot_forward_V(hot_ctx* ctx, const hot_slm* slm, int32_t B, const int32_t* M,
 
 /* Adjoint of Eq. 1: for a real loss L(V) and G_m = dL/dRe V_m + i dL/dIm V_m (device, 2T),
  *   grad_phase[b][j] = dL/dphi_j = (1/N) Im( exp(-i phi_j) sum_m G_m exp(i Delta_j^m) ),
- * with Delta recomputed (never stored).  phase device B x N, grad_phase device B x N. */
+ * with Delta recomputed (never stored).  phase device B x N, grad_phase device B x N.
+ * A G_m that is not finite makes its hologram's whole gradient non-finite, and no other's. */
 int hot_adjoint(hot_ctx* ctx, const hot_slm* slm, int32_t B, const int32_t* M, const double* xyz,
                 const float* phase, const float* G, float* grad_phase);
 

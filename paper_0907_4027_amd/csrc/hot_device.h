@@ -4,6 +4,8 @@
 
 #include "hot_internal.h"
 
+#include <type_traits>
+
 namespace hot {
 
 namespace {
@@ -56,6 +58,18 @@ __device__ __forceinline__ float wave_min(float v) {
   v = fminf(v, dpp<0x141>(v));
   v = fminf(v, dpp<0x140>(v));
   return fminf(fminf(rows_of(v, 0), rows_of(v, 16)), fminf(rows_of(v, 32), rows_of(v, 48)));
+}
+
+__device__ __forceinline__ unsigned wave_max_bits(unsigned v) {
+  auto dpp_max = [&](auto ctrl) {
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xF, 0xF, false));
+  };
+  dpp_max(std::integral_constant<int, 0xB1>{});
+  dpp_max(std::integral_constant<int, 0x4E>{});
+  dpp_max(std::integral_constant<int, 0x141>{});
+  dpp_max(std::integral_constant<int, 0x140>{});
+  auto row = [&](int lane) { return (unsigned)__builtin_amdgcn_readlane((int)v, lane); };
+  return max(max(row(0), row(16)), max(row(32), row(48)));
 }
 
 // A caller's phase [rad] in revolutions, reduced to [0, 1] (1 is the same angle as 0): product and

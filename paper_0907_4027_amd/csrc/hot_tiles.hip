@@ -136,14 +136,15 @@ __device__ __forceinline__ float2 unit_turn(float t) {
   return make_float2(c, s);
 }
 
-// E = S / |S|, 1 where S = 0 (arg 0 = 0), 0 outside the grid.  S is a sum of products of halves,
-// multiples of 2^-48, over weights scaled to at most 1: |S|^2 neither underflows nor overflows.
-__device__ __forceinline__ void unit_of(float x, float y, bool in, float& er, float& ei) {
+// E = e^{i phase_of(S)}: S / |S|, 1 where S = 0 or NaN (their phase is 0), 0 outside the grid.  After an
+// infinite weight (`inf`) S is NaN and so is E.  A finite S is a sum of products of halves, multiples of
+// 2^-48, over weights scaled to at most 1: |S|^2 neither underflows nor overflows.
+__device__ __forceinline__ void unit_of(float x, float y, bool in, bool inf, float& er, float& ei) {
   const float n2 = __builtin_fmaf(x, x, y * y);
   const float inv = __builtin_amdgcn_rsqf(n2);
-  const bool zero = n2 == 0.0f;
-  er = in ? (zero ? 1.0f : x * inv) : 0.0f;
-  ei = in && !zero ? y * inv : 0.0f;
+  const bool some = n2 > 0.0f || inf;
+  er = in ? (some ? x * inv : 1.0f) : 0.0f;
+  ei = in && some ? y * inv : 0.0f;
 }
 
 // sum over the lane's four rows of conj(y) t
@@ -180,23 +181,28 @@ struct TrapInputs {
   }
   // c_m of all traps into cw [Mp] (after the GS/GSW update where upd asks for it; the lead block also
   // writes the new state and keeps V in hist); returns the exponent that scales the largest below 1.
-  // Ends with a barrier; sh: 2 NW floats.
+  // `inf` tells of an infinite weight (and no NaN among them): a pair of halves cannot carry it (its low
+  // half is NaN), so S is NaN where the direct sums leave it infinite and its phase NaN.  Ends with a
+  // barrier; sh: 2 NW floats.
   __device__ __forceinline__ int weights(float2* cw, float* sh, int Mp, const TrapState* st_in, const float* vin,
-                                         int upd, bool lead, TrapState* st_out, float2* hist, int* flag) const {
+                                         int upd, bool lead, TrapState* st_out, float2* hist, int* flag,
+                                         bool& inf) const {
     const int wave = threadIdx.x >> 6;
-    float wmax = 0.0f;
+    unsigned top = 0u;  // bits of the largest magnitude: in the order of the magnitudes, infinity and NaN above all
+    auto take = [&](float w) { top = max(top, __builtin_bit_cast(unsigned, w) & 0x7fffffffu); };
     for (int m = M + (int)threadIdx.x; m < Mp; m += NT) cw[m] = make_float2(0.0f, 0.0f);
     if (MODE == 3) {
       for (int m = threadIdx.x; m < M; m += NT) {
         const float2 gm = make_float2(vin[2 * (off + m)], vin[2 * (off + m) + 1]);
         cw[m] = gm;
-        wmax = fmaxf(wmax, fmaxf(fabsf(gm.x), fabsf(gm.y)));
+        take(gm.x);
+        take(gm.y);
       }
     } else if (MODE == 2 || upd == 0) {
       for (int m = threadIdx.x; m < M; m += NT) {
         const TrapState s = m == (int)threadIdx.x ? s_first : st_in[off + m];
         cw[m] = trap_weight(s);
-        wmax = fmaxf(wmax, fabsf(s.w));
+        take(s.w);
       }
     } else {
       unsigned long long w8[kAccRegions];
@@ -213,18 +219,20 @@ struct TrapInputs {
       auto emit = [&](int m, const TrapState& st) {
         if (lead) st_out[off + m] = st;
         cw[m] = trap_weight(st);
-        wmax = fmaxf(wmax, fabsf(st.w));
+        take(st.w);
       };
       update_traps<NT, VAcc, decltype(emit), true>(vacc, st_in, off, M, upd, sh, nullptr, lead ? flag : nullptr, emit,
                                                    v_first, s_first);
     }
-    wmax = wave_max(wmax);
-    if ((threadIdx.x & 63) == 0) sh[NW + wave] = wmax;
+    top = wave_max_bits(top);
+    unsigned* tops = reinterpret_cast<unsigned*>(sh + NW);
+    if ((threadIdx.x & 63) == 0) tops[wave] = top;
     __syncthreads();
-    wmax = sh[NW];
+    top = tops[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) wmax = fmaxf(wmax, sh[NW + w]);
-    return __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(wmax));
+    for (int w = 1; w < NW; ++w) top = max(top, tops[w]);
+    inf = __builtin_amdgcn_readfirstlane((int)top) == 0x7f800000;
+    return __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(__builtin_bit_cast(float, top)));
   }
 };
 
@@ -415,7 +423,8 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
   auto inside = [&](int ct, int v) { return r < ny && c0 + 16 * ct + v < nx; };
 
   if constexpr (kPixel) {
-    wexp = in.weights(cw, sh, Mp, st_in, vin, upd, lead, st_out, hist, flag);
+    bool inf;
+    wexp = in.weights(cw, sh, Mp, st_in, vin, upd, lead, st_out, hist, flag, inf);
     // weighted Y of the first super-chunk
 #pragma unroll
     for (int j = 0; j < YK; ++j) {
@@ -508,7 +517,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
         for (int ct = 0; ct < CTW; ++ct) {
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            if (inside(ct, v)) phase[pix0 + 16 * ct + v] = phase_of(sim[ct][v], sre[ct][v]);
+            if (inside(ct, v)) phase[pix0 + 16 * ct + v] = inf ? __builtin_nanf("") : phase_of(sim[ct][v], sre[ct][v]);
         }
       }
       if constexpr (kTrap) {
@@ -517,7 +526,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
           float er[4], ei[4];
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            unit_of(sre[ct][v], sim[ct][v], inside(ct, v), er[v], ei[v]);
+            unit_of(sre[ct][v], sim[ct][v], inside(ct, v), inf, er[v], ei[v]);
           }
           put_e(ct, er, ei);
         }
@@ -739,7 +748,8 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
   auto inside = [&](int ct, int v) { return r < ny && c0 + 16 * ct + v < nx; };
 
   if constexpr (kPixel) {
-    const int wexp = in.weights(cw, sh, Mp, st_in, vin, upd, lead, st_out, hist, flag);
+    bool inf;
+    const int wexp = in.weights(cw, sh, Mp, st_in, vin, upd, lead, st_out, hist, flag, inf);
     for (int m = threadIdx.x; m < M; m += NT) {  // (each thread rescales the weights it wrote)
       const float2 c = cw[m];
       cw[m] = make_float2(__builtin_amdgcn_ldexpf(c.x, -wexp), __builtin_amdgcn_ldexpf(c.y, -wexp));
@@ -847,7 +857,7 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
         for (int ct = 0; ct < 2; ++ct) {
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            if (inside(ct, v)) phase[pix0 + 16 * ct + v] = phase_of(sim[ct][v], sre[ct][v]);
+            if (inside(ct, v)) phase[pix0 + 16 * ct + v] = inf ? __builtin_nanf("") : phase_of(sim[ct][v], sre[ct][v]);
         }
       }
       if constexpr (kTrap) {
@@ -855,7 +865,7 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
         for (int ct = 0; ct < 2; ++ct) {
           float er[4], ei[4];
 #pragma unroll
-          for (int v = 0; v < 4; ++v) unit_of(sre[ct][v], sim[ct][v], inside(ct, v), er[v], ei[v]);
+          for (int v = 0; v < 4; ++v) unit_of(sre[ct][v], sim[ct][v], inside(ct, v), inf, er[v], ei[v]);
           put_e(ct, er, ei);
         }
       }

@@ -157,3 +157,48 @@ def test_replays_of_long_solves_match_eager(hot, nx, ny, m):
             if rep % 2:
                 c.hot_gsw(q.slm, q.xyz, q.theta0, 2)  # another problem on the same buffers of the context
                 torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("nx,ny,m", [(70, 40, 9), (96, 64, 60), (700, 840, 20)])
+@pytest.mark.parametrize("algo_iters", [0, 3])
+def test_non_finite_weights(hot, nx, ny, m, algo_iters):
+    """A NaN weight makes every sum of Eq. 3 NaN, whose phase is 0: the mask is flat, V is the flat mask's
+    field, and neither is an error.  An infinite weight leaves no phase to return: the mask is NaN, its V 0
+    (the rounding of the trap sums), and the update meets <|V|> = 0.  Both as the direct sums have it."""
+    p = W.random_problem(946, nx, ny, m)
+    nan, inf = torch.ones(m, device="cuda"), torch.ones(m, device="cuda")
+    nan[m // 2] = float("nan")
+    inf[m // 2] = float("inf")
+    flat = oracle.forward(p.slm, p.xyz, np.zeros(nx * ny))
+    for knobs in ({}, {"rows": 1}):
+        with hot.Context(0) as c:
+            c.set_tuning(**knobs)
+            r = c.hot_gsw(p.slm, p.xyz, p.theta0, algo_iters, w0=nan, state=True)
+            assert not r.phase.any()
+            # the trap sums are rounded to 2^-30 per block (at most a thousand), the terms are FP32
+            assert np.abs(as_complex(to_np(r.V)) - flat).max() <= 5e-6
+            assert np.isfinite(r.stats).all()
+            w = to_np(r.w)
+            assert np.isnan(w[m // 2]) and np.isfinite(np.delete(w, m // 2)).all()
+            if algo_iters:
+                with pytest.raises(hot.HotError) as e:
+                    c.hot_gsw(p.slm, p.xyz, p.theta0, algo_iters, w0=inf)
+                assert e.value.code == hot.HOT_EDEGENERATE
+            r = c.hot_gsw(p.slm, p.xyz, p.theta0, algo_iters, w0=inf, stats=False)
+            assert torch.isnan(r.phase).all() and not r.V.any()
+
+
+def test_non_finite_gradients_stay_in_their_hologram(hot):
+    slm = W.Slm(70, 40)
+    rng = np.random.default_rng(6)
+    xyz = W.box_uniform(rng, 9)
+    phi = torch.tensor(rng.uniform(0, 6, (3, 40, 70)), dtype=torch.float32, device="cuda")
+    G = torch.tensor(rng.standard_normal((9, 2)), dtype=torch.float32, device="cuda")
+    with hot.Context(0) as c:
+        ref = c.hot_adjoint(slm, [3, 3, 3], xyz, phi, G)
+        for bad in (float("nan"), float("inf"), -float("inf")):
+            H = G.clone()
+            H[4, 1] = bad
+            g = c.hot_adjoint(slm, [3, 3, 3], xyz, phi, H)
+            assert not torch.isfinite(g[1]).any()
+            assert torch.equal(g[0], ref[0]) and torch.equal(g[2], ref[2])
