@@ -60,12 +60,16 @@ constexpr int kGraphCache = 128;
 // masks whose V is kept before their figures of merit are taken, and the memory that may take
 constexpr int kHistMasks = 64;
 constexpr int64_t kHistBytes = int64_t(64) << 20;
-// Solves of at most this many iterations are launched eagerly: starting a replay costs about 5 us more
-// than the same launches one by one, which the host gives out faster (2-3 us each) than the device
-// works them off (4 us and more).  Per solve, eagerly against by replay: random superposition 128 x 96
-// x 10 traps 22 against 48 us; GSW 256^2 x 16 with 3 / 10 / 20 iterations 27 / 59 / 101 against 33 /
-// 63 / 107 us, 512^2 x 100 39 / 88 / 158 against 44 / 94 / 164 us.  Longer sequences keep the host free
-// with one replay, for 1-2 %.
+// Solves of at most this many iterations are launched eagerly where that is the faster way: starting a
+// replay costs about 5 us more than the same launches one by one, which the host gives out faster (2-3 us
+// each) than the device works them off (4 us and more).  Per solve, eagerly against by replay: random
+// superposition 128 x 96 x 10 traps 22 against 48 us; GSW 256^2 x 16 with 3 / 10 / 20 iterations
+// 27 / 59 / 101 against 33 / 63 / 107 us, 512^2 x 100 39 / 88 / 158 against 44 / 94 / 164 us.  Longer
+// sequences keep the host free with one replay, for 1-2 %.  Not so for the stored variant, whose four
+// launches of 3 us per iteration the host cannot keep up with (128 x 96 x 10, 10 iterations: 155 against
+// 120 us), nor for the kernels that launch-shape knobs select when a copy of the statistics follows the
+// launches (256^2 x 16, 24 iterations: 214 against 196 us; without statistics 149 against 148, and 10
+// iterations 70 against 73): these replay from the first iteration on.
 constexpr int kEagerIters = 24;
 constexpr double kPi = 3.14159265358979323846;
 
@@ -813,7 +817,8 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   // Replay a captured graph of the sequence when one with the same shapes and pointers
   // exists (captured on the context's own stream, launched on the caller's).
   bool done = false;
-  if (c->use_graphs && K > kEagerIters) {
+  const int eager = tiles || (!stored && !stats) ? kEagerIters : stored && stats ? -1 : 0;
+  if (c->use_graphs && K > eager) {
     // everything a launch of the sequence is made of that may differ between calls: the largest trap
     // count too, which sets the dynamic LDS and strides of a batch's launches (each hologram's own count
     // is read on the device)
