@@ -111,7 +111,8 @@ int hot_set_variant(hot_ctx* ctx, int variant);
 /* Launch-shape knobs (used by the autotuner; 0 restores the built-in choice, except
  * HOT_TUNE_GRAPHS).  They change how work is tiled or launched, never what is computed
  * beyond FP32 rounding.  With every knob of a variant at 0 it runs on the tile kernels, which choose
- * their own shapes; a HOT_TUNE_SEP knob selects the FP32 matrix kernels of the separable variant, any
+ * their own shapes (but for hundreds of traps on masks of a few thousand pixels, where the direct sums of
+ * the on-the-fly variant are faster); a HOT_TUNE_SEP knob selects the FP32 matrix kernels of the separable variant, any
  * other knob (but HOT_TUNE_GRAPHS) the direct-sum kernels of the on-the-fly variant, and the built-in
  * choices named below are those kernels' own. */
 enum hot_tuning_key {
@@ -125,8 +126,9 @@ enum hot_tuning_key {
   HOT_TUNE_SLICES = 4,          /* trap pass: at most this many pixel slices per wave, 1..16 */
   HOT_TUNE_GRAPHS = 5,          /* 1 (default): replay a captured hipGraph of a solve's launch
                                    sequence when shapes and buffers repeat (solves of at most 24
-                                   iterations are launched eagerly: a replay costs about 5 us
-                                   more than their launches); 0: launch eagerly */
+                                   iterations are launched eagerly where a replay, which costs
+                                   about 5 us more than their launches, gains nothing);
+                                   0: launch eagerly */
   HOT_TUNE_SEP_WAVES = 6,       /* separable variant: tiles of 16 x 16 pixels per block (1, 2 or 4),
                                    one or two waves each (HOT_TUNE_SEP_SPLIT) */
   HOT_TUNE_SEP_CHUNK = 7,       /* separable variant: traps whose tables a block holds in LDS at

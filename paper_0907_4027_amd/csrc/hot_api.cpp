@@ -116,6 +116,7 @@ struct hot_ctx {
   bool na_pending = false;
   // identity of the trap tables now on the device (skips re-upload and stored-matrix rebuilds)
   std::vector<double> key;
+  bool hd_lanes = false;  // whether the uploaded descriptors hold lane layouts (the direct sums')
   bool amat_valid = false;
   std::vector<TrapCoef> h_coef;
   std::vector<TrapState> h_st;
@@ -311,13 +312,35 @@ FwdGeom row_segments(int nx, int ny, int segmax) {
   return f;
 }
 
-// Whether the on-the-fly or separable variant runs on the tile kernels: always, unless a launch-shape
-// knob of that variant's other kernels is set (the direct-sum kernels' for the on-the-fly variant, the
-// FP32 matrix kernels' for the separable one), which selects those.
-bool use_tiles(const hot_ctx* c, int variant) {
+// What a call computes, where the choice of kernels depends on it.
+enum class Job { kSolve, kField, kAdjoint };
+
+// Whether the on-the-fly or separable variant runs on the tile kernels.  A launch-shape knob of that
+// variant's other kernels (the direct-sum kernels' for the on-the-fly variant, the FP32 matrix kernels'
+// for the separable one) selects those.  Else always, but for very many traps on small masks: a block of
+// the tile kernels then works off its traps one super-chunk after the other, on a few compute units of
+// the chip, while the direct sums have a block per row.
+//   Solves: a row's time grows with its length, so the line lies at ten traps per column (direct against
+//   tile kernels, us per GSW solve of 5 / 40 iterations: 16^2 x 1024 222 / 1410 against 251 / 1664,
+//   64^2 x 1024 240 / 1540 against 257 / 1705, 96 x 80 x 1024 253 / 1624 against 258 / 1715, 128^2 x 1024
+//   265 / 1709 against 257 / 1711, 128^2 x 2048 489 / 3248 against 502 / 3382; 32^2 x 384 110 against
+//   103), and while the rows of all holograms find a unit each (8 of 32^2 x 2048 433 against 511, 16 of
+//   them 601 against 523).
+//   Eq. 1 of one mask: above 896 traps (64^2 x 768 19.4 against 18.4, x 1024 20.5 against 23.0, x 2048
+//   24.8 against 41.9; 4096 x 1 x 896 25.8 against 22.0, x 960 22.7 against 23.7) while its blocks of 256
+//   pixels are at most three quarters of the units (192^2 x 2048 35.9 against 43.0, 256^2 x 2048 45.7
+//   against 43.9).  For several masks the search for the lane layouts, on the host, costs more than the
+//   sums save (4 of 64^2 x 2048 65 against 49).
+// The adjoint is faster on the tile kernels throughout (64^2 x 2048 37 against 49).
+bool use_tiles(const hot_ctx* c, int variant, Job job, int nx, int ny, int B, int mmax) {
   if (variant == HOT_STORED) return false;
   if (variant == HOT_SEPARABLE) return !c->tune_sepw && !c->tune_sepc && !c->tune_sepk;
-  return !c->tune_q && !c->tune_tpl && !c->tune_seg && !c->tune_amax && !c->tune_rows && !c->tune_fract;
+  if (c->tune_q || c->tune_tpl || c->tune_seg || c->tune_amax || c->tune_rows || c->tune_fract) return false;
+  if (job == Job::kSolve)
+    return !(mmax >= 512 && mmax >= 10 * nx && nx <= 128 && (int64_t)ny * B <= c->num_cu);
+  if (job == Job::kField)
+    return !(B == 1 && mmax > 896 && 4 * (int64_t)row_segments(nx, ny, kSpan).nblk() <= 3 * c->num_cu);
+  return true;
 }
 
 // Block shape and super-chunk of the tile kernels.
@@ -351,11 +374,10 @@ void choose_tile(const hot_ctx* c, Plan& P) {
 
 // Build the coefficient, state and descriptor tables of a problem on the host, into coef_out [T],
 // st_out [T] and hd_out [2B] (the fused kernel's layouts, then the stand-alone trap pass's; without
-// lane layouts when `variant` runs on the tile kernels, which need none).
-int prepare_into(hot_ctx* c, int variant, const hot_slm* slm, int B, const int32_t* counts, const double* xyz,
+// lane layouts when the call runs on the tile kernels, which need none).
+int prepare_into(hot_ctx* c, int variant, Job job, const hot_slm* slm, int B, const int32_t* counts, const double* xyz,
                  const double* theta0, bool seeded, uint64_t seed, Plan& P, TrapCoef* coef_out, TrapState* st_out,
                  HoloDesc* hd_out) {
-  P.tiles = use_tiles(c, variant);
   P.B = B;
   P.nx = slm->nx;
   P.ny = slm->ny;
@@ -374,6 +396,7 @@ int prepare_into(hot_ctx* c, int variant, const hot_slm* slm, int B, const int32
     P.T += counts[b];
     P.mmax = std::max(P.mmax, (int)counts[b]);
   }
+  P.tiles = use_tiles(c, variant, job, P.nx, P.ny, B, P.mmax);
   // fused kernel shape
   {
     const int q = c->tune_q == 2 ? 2 : 1;
@@ -536,14 +559,14 @@ int prepare_into(hot_ctx* c, int variant, const hot_slm* slm, int B, const int32
   return HOT_OK;
 }
 
-int prepare(hot_ctx* c, int variant, const hot_slm* slm, int B, const int32_t* counts, const double* xyz, const double* theta0,
-            bool seeded, uint64_t seed, Plan& P) {
+int prepare(hot_ctx* c, int variant, Job job, const hot_slm* slm, int B, const int32_t* counts, const double* xyz,
+            const double* theta0, bool seeded, uint64_t seed, Plan& P) {
   int64_t T = 0;
   for (int b = 0; b < B; ++b) T += counts[b];
   c->h_coef.resize(T);
   c->h_st.resize(T);
   c->h_hd.resize(2 * (size_t)B);
-  return prepare_into(c, variant, slm, B, counts, xyz, theta0, seeded, seed, P, c->h_coef.data(), c->h_st.data(),
+  return prepare_into(c, variant, job, slm, B, counts, xyz, theta0, seeded, seed, P, c->h_coef.data(), c->h_st.data(),
                       c->h_hd.data());
 }
 
@@ -565,13 +588,13 @@ int upload_tables(hot_ctx* c, const hot_slm* slm, const Plan& P, const double* x
   key.push_back(c->tune_seg);
   key.push_back(c->tune_amax);
   key.push_back(c->tune_sepw);
-  key.push_back(P.tiles);
   key.push_back(P.B);
   for (int b = 0; b < P.B; ++b) key.push_back(counts[b]);
   key.insert(key.end(), xyz, xyz + 3 * (size_t)P.T);
   int rc;
   if ((rc = ensure(c, c->st, 2 * sizeof(TrapState) * P.T))) return rc;
-  const bool fresh = !(key == c->key && c->coef.p && c->hd.p);
+  // (descriptors with lane layouts serve the tile kernels too, which read counts and offsets only)
+  const bool fresh = !(key == c->key && c->coef.p && c->hd.p && (P.tiles || c->hd_lanes));
   if (fresh) {
     c->key.clear();
     c->amat_valid = false;
@@ -600,7 +623,10 @@ int upload_tables(hot_ctx* c, const hot_slm* slm, const Plan& P, const double* x
   HIP_TRY(launch_upload(c->stream, u));
   HIP_TRY(hipEventRecord(s->ev, c->stream));
   s->pending = true;
-  if (fresh) c->key.swap(key);
+  if (fresh) {
+    c->key.swap(key);
+    c->hd_lanes = !P.tiles;
+  }
   return HOT_OK;
 }
 
@@ -706,7 +732,7 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   int rc;
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, variant, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
+  if ((rc = prepare(c, variant, Job::kSolve, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
   const int K = algo == kRS ? 0 : iters;
   const bool stored = variant == HOT_STORED;
   const bool separable = variant == HOT_SEPARABLE;
@@ -1139,8 +1165,8 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     c->na_pending = false;
   }
   Plan P;
-  if ((rc = prepare_into(c, HOT_ONTHEFLY, slm, 1, &M, xyz, theta0, theta0 == nullptr, seed, P, (TrapCoef*)(c->na_host + L.coef),
-                         (TrapState*)(c->na_host + L.st), (HoloDesc*)(c->na_host + L.hd))))
+  if ((rc = prepare_into(c, HOT_ONTHEFLY, Job::kSolve, slm, 1, &M, xyz, theta0, theta0 == nullptr, seed, P,
+                         (TrapCoef*)(c->na_host + L.coef), (TrapState*)(c->na_host + L.st), (HoloDesc*)(c->na_host + L.hd))))
     return rc;
   char* base = (char*)c->scratch;
   TrapState* st[2] = {(TrapState*)(base + L.st), (TrapState*)(base + L.st) + M};
@@ -1303,7 +1329,7 @@ int hot_forward_V(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M, c
   if ((rc = set_dev(c))) return rc;
   Plan P;
   std::vector<double> zeros(T, 0.0);
-  if ((rc = prepare(c, fa_variant(c), slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
+  if ((rc = prepare(c, fa_variant(c), Job::kField, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, M, false))) return rc;
   if (P.tiles) {
     if ((rc = ensure(c, c->partial, sizeof(float2) * (size_t)P.T * P.nblk_tile))) return rc;
@@ -1340,7 +1366,7 @@ int hot_adjoint(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M, con
   if ((rc = set_dev(c))) return rc;
   Plan P;
   std::vector<double> zeros(T, 0.0);
-  if ((rc = prepare(c, fa_variant(c), slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
+  if ((rc = prepare(c, fa_variant(c), Job::kAdjoint, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, M, false))) return rc;
   if (P.tiles) {
     SepArgs a = tile_args(c, P, 3, const_cast<float*>(phase), 0);
@@ -1381,7 +1407,7 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   if (reps < 1) return fail(HOT_EINVAL, "reps = %d < 1", reps);
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, c->variant, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
+  if ((rc = prepare(c, c->variant, Job::kSolve, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
   const bool stored = c->variant == HOT_STORED;
   const bool separable = c->variant == HOT_SEPARABLE;
   const bool tiles = P.tiles;
@@ -1515,7 +1541,7 @@ int hot_pixel_pass_variant(hot_ctx* c, const hot_slm* slm, int32_t M, const doub
   if (reps < 1) return fail(HOT_EINVAL, "reps = %d < 1", reps);
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, HOT_ONTHEFLY, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
+  if ((rc = prepare(c, HOT_ONTHEFLY, Job::kSolve, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, &M))) return rc;
   const int nb = abl_blocks(mapping, block, slm->nx, slm->ny);
   if ((rc = ensure(c, c->abl, sizeof(float4) * (size_t)nb * M))) return rc;

@@ -202,3 +202,52 @@ def test_non_finite_gradients_stay_in_their_hologram(hot):
             g = c.hot_adjoint(slm, [3, 3, 3], xyz, phi, H)
             assert not torch.isfinite(g[1]).any()
             assert torch.equal(g[0], ref[0]) and torch.equal(g[2], ref[2])
+
+
+@pytest.mark.parametrize("nx,ny,m", [(16, 16, 512), (51, 40, 512), (52, 40, 512), (128, 120, 1280), (96, 257, 1000)])
+def test_many_traps_on_small_masks(hot, nx, ny, m):
+    """The direct sums take over for many traps on small masks (same bits as with a knob that selects them
+    and is their default); either side of the line matches the oracle."""
+    p = W.random_problem(947, nx, ny, m)
+    direct = m >= 10 * nx and ny <= 256
+    with hot.Context(0) as c, hot.Context(0) as k:
+        k.set_tuning(rows=1)
+        a, b, n = (f(p.slm, p.xyz, p.theta0, 2) for f in (c.hot_gsw, k.hot_gsw, c.hot_gsw_noalloc))
+        r = c.hot_rs(p.slm, p.xyz, p.theta0)
+        torch.cuda.synchronize()
+    assert torch.equal(a.phase, b.phase) == direct
+    assert torch.equal(a.phase, n.phase) and torch.equal(a.V, n.V)
+    o = oracle.solve("rs", p.slm, p.xyz, p.theta0, 0)
+    assert_phase(to_np(r.phase), o["phi"])
+    # |V| is of size sqrt(1 / M) here: the bar is on the scale of its terms
+    assert np.abs(as_complex(to_np(r.V)) - o["V"]).max() <= 5e-6
+
+
+@pytest.mark.parametrize("nx,ny,counts", [(64, 40, [896]), (64, 40, [897]), (300, 96, [1000]), (300, 97, [1000]),
+                                          (33, 20, [1000, 900])])
+def test_fields_of_many_traps_beside_their_adjoint(hot, nx, ny, counts):
+    """Eq. 1 of one small mask of very many traps runs on the direct sums, its adjoint on the tile kernels:
+    in turn on one context, with the tables of either, they match the oracle and themselves."""
+    rng = np.random.default_rng(nx + ny)
+    slm, T, B = W.Slm(nx, ny), int(sum(counts)), len(counts)
+    xyz = W.box_uniform(rng, T)
+    phi = rng.uniform(0.0, 6.0, (B, ny, nx)).astype(np.float32)
+    G = rng.standard_normal((T, 2)).astype(np.float32)
+    dphi, dG = torch.tensor(phi, device="cuda"), torch.tensor(G, device="cuda")
+    direct = B == 1 and T > 896 and -(-nx // 256) * ny <= 192
+    with hot.Context(0) as c, hot.Context(0) as k:
+        k.set_tuning(rows=1)
+        V = [c.hot_forward_V(slm, counts, xyz, dphi)]
+        g = [c.hot_adjoint(slm, counts, xyz, dphi, dG)]
+        V.append(c.hot_forward_V(slm, counts, xyz, dphi))
+        g.append(c.hot_adjoint(slm, counts, xyz, dphi, dG))
+        assert torch.equal(V[0], k.hot_forward_V(slm, counts, xyz, dphi)) == direct
+        torch.cuda.synchronize()
+    assert torch.equal(V[0], V[1]) and torch.equal(g[0], g[1])
+    o = 0
+    for b, m in enumerate(counts):
+        flat = phi[b].ravel().astype(np.float64)
+        assert np.abs(as_complex(to_np(V[0][o:o + m])) - oracle.forward(slm, xyz[o:o + m], flat)).max() <= 2e-6
+        gr = oracle.adjoint(slm, xyz[o:o + m], flat, G[o:o + m, 0].astype(np.float64) + 1j * G[o:o + m, 1])
+        assert relative(to_np(g[0][b]).ravel(), np.ravel(gr)) <= 2e-6
+        o += m
