@@ -15,7 +15,8 @@ For one problem shape it times every candidate combination of
 with ``hot_time_passes`` (HIP events around back-to-back launches on the context's stream),
 beside the library's own choice (every knob 0: the tile kernels; any of these knobs selects the
 direct-sum kernels), keeps the fastest fused-iteration kernel, and caches it in a JSON file keyed by
-(architecture, variant, grid, trap-count bucket).  The sweep table doubles as an
+(architecture, variant, grid, trap-count bucket).  An entry counts only for the kernels it was measured
+on (``KERNELS``): any other is measured again and replaced.  The sweep table doubles as an
 ablation of the kernel's shape choices on this GPU.  Only launch shapes change --
 results differ at most by FP32 summation order.
 """
@@ -36,6 +37,9 @@ CANDIDATES = {
     "traps_per_lane": (0, 2, 3, 4, 5, 6, 8),
     "rows": (1, 2),
 }
+# Names what the knobs choose among.  Entries from before the tile kernels carry no such name: each sets a
+# knob, and any knob now selects the direct sums, up to six times slower than the library's own choice.
+KERNELS = "tiles"
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "hot_mi355x", "tuning.json")
 
 
@@ -49,6 +53,17 @@ def _bucket(m: int) -> int:
 def cache_key(ctx: Context, slm, m: int, variant: str = "onthefly") -> str:
     arch = torch.cuda.get_device_properties(ctx.device).gcnArchName.split(":")[0]
     return f"{arch}/{variant}/{int(slm.nx)}x{int(slm.ny)}/M{_bucket(m)}"
+
+
+def _load(cache: Optional[str]) -> dict:
+    if not (cache and os.path.exists(cache)):
+        return {}
+    with open(cache) as f:
+        return json.load(f)
+
+
+def _known(db: dict, key: str) -> bool:
+    return key in db and db[key].get("kernels") == KERNELS
 
 
 def sweep(ctx: Context, slm, xyz, theta0, reps: int = 20, candidates: Optional[dict] = None) -> list:
@@ -77,16 +92,13 @@ def tune(ctx: Context, slm, xyz, theta0, cache: Optional[str] = DEFAULT_CACHE, r
     """Best knobs for this problem shape (from the cache, or measured and cached); applied to
     ctx when `apply`.  Returns {"key", "knobs", "table" (None on a cache hit)}."""
     key = cache_key(ctx, slm, len(xyz))
-    db = {}
-    if cache and os.path.exists(cache):
-        with open(cache) as f:
-            db = json.load(f)
+    db = _load(cache)
     table = None
-    if key not in db:
+    if not _known(db, key):
         table = sweep(ctx, slm, xyz, theta0, reps=reps)
         best = table[0]
         db[key] = {k: best[k] for k in ("pixels_per_lane", "segment", "traps_per_lane", "rows")} | \
-                  {"iteration_us": best["iteration_us"]}
+                  {"iteration_us": best["iteration_us"], "kernels": KERNELS}
         if cache:
             os.makedirs(os.path.dirname(cache), exist_ok=True)
             with open(cache, "w") as f:
@@ -115,8 +127,8 @@ def batch_key(ctx: Context, slm, counts, variant: str = "onthefly") -> str:
 
 def sweep_batched(ctx: Context, slm, counts, xyz, theta0, iters: int = 2, reps: int = 3,
                   candidates: Optional[dict] = None) -> list:
-    """Time hot_gsw_batched (a short solve of `iters` iterations, graph-replayed) for every knob
-    combination; rows sorted by device milliseconds per solve."""
+    """Time hot_gsw_batched (a short solve of `iters` iterations) for every knob combination (and, without
+    `candidates`, the library's own choice); rows sorted by device milliseconds per solve."""
     import numpy as np
     cand = candidates or BATCH_CANDIDATES
     cnt = np.asarray(counts, dtype=np.int32)
@@ -150,16 +162,13 @@ def tune_batched(ctx: Context, slm, counts, xyz, theta0, cache: Optional[str] = 
                  reps: int = 3, apply: bool = True) -> dict:
     """Best knobs for this batch shape (cached like ``tune``); applied to ctx when `apply`."""
     key = batch_key(ctx, slm, counts)
-    db = {}
-    if cache and os.path.exists(cache):
-        with open(cache) as f:
-            db = json.load(f)
+    db = _load(cache)
     table = None
-    if key not in db:
+    if not _known(db, key):
         table = sweep_batched(ctx, slm, counts, xyz, theta0, iters=iters, reps=reps)
         best = table[0]
         db[key] = {k: best[k] for k in ("traps_per_lane", "rows", "pixels_per_lane")} | \
-                  {"ms_per_solve": best["ms_per_solve"]}
+                  {"ms_per_solve": best["ms_per_solve"], "kernels": KERNELS}
         if cache:
             os.makedirs(os.path.dirname(cache), exist_ok=True)
             with open(cache, "w") as f:
