@@ -110,6 +110,14 @@ __device__ __forceinline__ float sum_groups(float2 a, float2 b) {
   return r.x + r.y;
 }
 
+// Between words of LDS that a wave's lanes write and other lanes of the same wave read: the wave's accesses
+// are carried out in program order, and this keeps the compiler to it.  No instruction of its own.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A fragment of a table: 16 rows or columns x 16 traps of complex entries, each a word of two halves
 // (re, im).  Entry (i, t) of the hi part is word 4 i + 132 (t / 4) + t % 4, of the lo part 64 words
 // further: a lane's four consecutive traps are one 16-byte read (matrix operand with the traps as
@@ -327,6 +335,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
       const int m = 16 * (jy + YS * j) + li;
       ry[m] = group(coef[off + min(k0 + m, M - 1)], coef[off + min(k0 + m, M - 1)].b, Yc);
     }
+    wave_order();  // (the entries are formed from other lanes' constants)
   };
   auto entries = [&](const float4* ks, int tt, float2 (&e)[4]) {
     const float4 k = ks[16 * tt + li];
@@ -710,6 +719,7 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
     const int nt = n >> 4;
     ref_store(first, n, 0);
     for (int round = 1; part + 4 * round < nt; ++round) ref_store(ref_load(k0, round), n, round);
+    wave_order();  // (the entries are formed from other lanes' constants)
 #pragma unroll 2
     for (int tt = part; tt < nt; tt += 2) {
       const int i = tt >> 1;
