@@ -58,3 +58,49 @@ def test_batches_of_other_counts_do_not_share_a_replay(hot, variant, knobs, n, f
             r = c.hot_gsw_batched(slm, counts, xyz, theta0, ITERS, phase=phase, V=V)
             assert torch.equal(r.phase, ref.phase) and torch.equal(r.V, ref.V), counts
             np.testing.assert_array_equal(r.stats, ref.stats)
+
+
+# every kernel family behind a solve: (variant, knobs, grid, trap counts)
+FAMILIES = [("stored", {}, (130, 70), [17]),
+            ("onthefly", {"rows": 1}, (300, 77), [37]),
+            ("onthefly", {"rows": 2}, (120, 90), [5, 64, 20]),
+            ("separable", {"sep_split": 1}, (150, 90), [40]),
+            ("separable", {"sep_split": 2}, (96, 64), [33, 7]),
+            ("separable", {}, (130, 70), [60]),
+            ("onthefly", {}, (64, 60), [700]),
+            ("onthefly", {}, (96, 64), [5, 64, 20]),
+            ("onthefly", {}, (520, 500), [60, 3, 100, 40])]
+
+
+@pytest.mark.parametrize("variant,knobs,grid,counts", FAMILIES)
+@pytest.mark.parametrize("stats", [False, True])
+def test_replays_match_eager(hot, variant, knobs, grid, counts, stats):
+    """Several replays, with other work and synchronisations between them."""
+    (nx, ny), B, T = grid, len(counts), sum(counts)
+    slm = W.Slm(nx, ny)
+    xyz, theta0 = batch(4, counts)
+    q = W.random_problem(950, 80, 60, 7, 2)
+    with hot.Context(0) as eager, hot.Context(0) as c:
+        for x in (eager, c):
+            x.set_variant(variant)
+            x.set_tuning(**knobs)
+        eager.set_graphs(False)
+        phase = torch.empty(*((B,) if B > 1 else ()), ny, nx, device="cuda")
+        V = torch.empty(T, 2, device="cuda")
+        if B > 1:
+            run = lambda x, **out: x.hot_gsw_batched(slm, counts, xyz, theta0, ITERS, stats=stats, **out)
+        else:
+            run = lambda x, **out: x.hot_gsw(slm, xyz, theta0, ITERS, stats=stats, **out)
+        ref = run(eager)
+        for rep in range(4):
+            phase.zero_()
+            V.zero_()
+            r = run(c, phase=phase, V=V)
+            torch.cuda.synchronize()
+            assert torch.equal(r.phase, ref.phase) and torch.equal(r.V, ref.V), rep
+            if stats:
+                np.testing.assert_array_equal(r.stats, ref.stats)
+            if rep % 2:
+                c.hot_gsw(q.slm, q.xyz, q.theta0, 2)  # another problem on the same buffers of the context
+                torch.randn(1 << 20, device="cuda").sum()
+                torch.cuda.synchronize()
