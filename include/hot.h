@@ -83,7 +83,9 @@ enum hot_status {
  * The on-the-fly (default) and the separable variant both run on the tile kernels: for each tile of
  * pixels the two factors of exp(i Delta) = X_m(column) Y_m(row), exact for Eq. 2, are recomputed with
  * FP32 sin/cos and contracted on the FP16 matrix cores, every factor carried as a pair of halves
- * (22 bits and more) and summed in FP32: the accuracy of FP32 products.  Setting a launch-shape knob of
+ * (22 bits and more) and summed in FP32: the accuracy of FP32 products.  Weights and gradients are split
+ * relative to the largest of their hologram: one that is smaller by 2^k keeps about 25 - k bits, none from
+ * 2^-25 on, which is where an FP32 sum beside the largest loses them too.  Setting a launch-shape knob of
  * a variant's other kernels (hot_set_tuning) selects those instead. */
 enum hot_variant {
   HOT_ONTHEFLY = 0, /* Delta recomputed on the fly (default).  With a knob of the direct sums set: per

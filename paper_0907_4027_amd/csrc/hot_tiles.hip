@@ -13,12 +13,17 @@
 // rate of the FP32 products (16 cycles for 16 x 16 x 32 against 32 for 16 x 16 x 4).  Every real factor v
 // (|v| <= 1) is carried as hi = f16(v), lo = f16(v - hi), which leaves |v - hi - lo| <= 2^-24, the
 // rounding of an FP32 value just below 1, and a product is hi hi + hi lo + lo hi (the dropped lo lo is
-// below 2^-24): three half products for one FP32 product.  Measured against 64 bits over grids of 48 to
-// 2048 pixels a side and 3 to 1000 traps, fields and gradients are as close as with FP32 matrix products
-// (2.3e-7 against 3.3e-7 relative for the adjoint of 8 x 512^2 x 64) and closer than the direct sums
-// (7.2e-7), whose per-term arguments reach several revolutions.  The weights are scaled by a power of two
-// so that the largest is below 1; all the rest (arguments, sine and cosine, normalisation, trap sums) is
-// FP32 or FP64 as in the other kernels.
+// below 2^-24): three half products for one FP32 product.  (The adjoint scales by the larger component of
+// G, so a factor there reaches sqrt 2, and both bounds above 1 are 2^-23.)  Measured against 64 bits over
+// grids of 48 to 2048 pixels a side and 3 to 1000 traps, fields and gradients are as close as with FP32
+// matrix products (2.3e-7 against 3.3e-7 relative for the adjoint of 8 x 512^2 x 64) and closer than the
+// direct sums (7.2e-7), whose per-term arguments reach several revolutions.  The weights are scaled by a
+// power of two so that the largest is below 1: a weight keeps an error of 2^-25 of the largest however
+// small it is itself, while an FP32 sum rounds by as much at each of its terms.  Weights and G spread over
+// 0 to 12 decades (512^2 x 100): masks 5.7e-7 .. 9.4e-7 rad rms from 64 bits at every spread (direct sums
+// 1.7e-6 .. 4.8e-6, FP32 matrix products 6.9e-7 .. 1.3e-6), V within 2.1e-7 (2.6e-7, 2.0e-7), gradients
+// 2.4e-7 .. 3.1e-7 relative (5.0e-7 .. 9.2e-7, 3.5e-7 .. 4.0e-7).  All the rest (arguments, sine and
+// cosine, normalisation, trap sums) is FP32 or FP64 as in the other kernels.
 //
 // MFMA 16x16x32 operands: lane l = i + 16 g holds A[i][8 g ..+7] and B[8 g ..+7][i]; result D[i][j] is in
 // lane j + 16 (i / 4), register i % 4.  Eight halves are four complex entries (re, im), so a product

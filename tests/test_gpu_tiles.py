@@ -251,3 +251,22 @@ def test_fields_of_many_traps_beside_their_adjoint(hot, nx, ny, counts):
         gr = oracle.adjoint(slm, xyz[o:o + m], flat, G[o:o + m, 0].astype(np.float64) + 1j * G[o:o + m, 1])
         assert relative(to_np(g[0][b]).ravel(), np.ravel(gr)) <= 2e-6
         o += m
+
+
+@pytest.mark.parametrize("decades", [2, 6, 12])
+def test_fields_and_gradients_of_widely_spread_weights(hot, decades):
+    """Weights and G over many decades are split relative to the largest: V of the mask and the gradient
+    stay within the bars of equal ones (their errors are those of the largest terms)."""
+    p = W.random_problem(948, 200, 150, 50)
+    rng = np.random.default_rng(decades)
+    w = rng.permutation(np.logspace(-decades / 2, decades / 2, p.m))
+    w0 = torch.tensor(w, dtype=torch.float32, device="cuda")
+    phi = rng.uniform(0.0, 6.0, (1, 150, 200)).astype(np.float32)
+    G = (rng.standard_normal((p.m, 2)) * w[:, None]).astype(np.float32)
+    with hot.Context(0) as c:
+        r = c.hot_gsw(p.slm, p.xyz, p.theta0, 0, w0=w0)
+        g = to_np(c.hot_adjoint(p.slm, [p.m], p.xyz, torch.tensor(phi, device="cuda"), torch.tensor(G, device="cuda")))
+    mask = oracle.backward(p.slm, p.xyz, to_np(w0), p.theta0)
+    assert np.abs(as_complex(to_np(r.V)) - oracle.forward(p.slm, p.xyz, mask)).max() <= 2e-6
+    ref = oracle.adjoint(p.slm, p.xyz, phi.ravel().astype(np.float64), G[:, 0].astype(np.float64) + 1j * G[:, 1])
+    assert relative(g.ravel(), np.ravel(ref)) <= 2e-6
