@@ -260,25 +260,25 @@ struct TrapInputs {
 // MODE 2: pixel pass alone from the given state (phase out)
 // MODE 3: adjoint of Eq. 1: weights G_m (vin), grad[j] = (1/N) Im(e^{-i phi_j} S_j) for the given phase
 //
-// Grid (ceil(nx / 16 CW CTW), ceil(ny / 16 RT), B), RT CW KH waves: wave (rt, cwv, part) has row tile
-// rt, column tiles CTW cwv .. + CTW - 1 and share `part` of the trap tiles of each super-chunk (mc traps);
+// Grid (ceil(nx / 16 CW), ceil(ny / 16 RT), B), RT CW KH waves: wave (rt, cwv, part) has row tile rt,
+// column tile cwv and share `part` of the trap tiles of each super-chunk (mc traps);
 // the KH partial pixel sums of a tile meet in LDS and are added in a fixed order.  The waves build the
 // tables together: a wave always has the same column tile tx and row tile ty, whose group constants
 // (the phase about the tile's centre column or row, formed in FP64 and rounded once; K, slope, curvature)
 // it forms for itself, so no barrier stands between them and the entries.  Columns past nx and rows past
 // ny get the formula's values and pixels with E = 0; traps past M repeat trap M - 1 with weight 0.
 // Dynamic LDS: tile_lds_bytes.
-template <int RT, int CW, int CTW, int KH, int MODE>
-__global__ void __launch_bounds__(RT * CW * KH * 64, RT * CW * KH >= 16 ? 4 : 2)
+template <int RT, int CW, int KH, int MODE>
+__global__ void __launch_bounds__(RT * CW * KH * 64, 2)
 k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
        const unsigned long long* __restrict__ acc_in, int one_m, int one_off, int T, float unscale, int nx, int ny,
        int mc, int upd, const HoloDesc* __restrict__ hd, TrapState* __restrict__ st_out,
        const float* __restrict__ vin, float2* __restrict__ hist, int* __restrict__ flag, float inv_n,
        float* __restrict__ phase, float* __restrict__ grad, float2* __restrict__ partial,
        unsigned long long* __restrict__ acc_out, unsigned long long* __restrict__ acc_zero, float scale) {
-  constexpr int NS = RT * CW, NW = NS * KH, NT = NW * 64, CT = CW * CTW;
-  constexpr int XS = NW / CT, YS = NW / RT;  // waves sharing a column tile's (row tile's) table
-  static_assert(NW % CT == 0 && NW % RT == 0, "whole waves per column and row tile");
+  constexpr int NS = RT * CW, NW = NS * KH, NT = NW * 64;
+  constexpr int XS = NW / CW, YS = NW / RT;  // waves sharing a column tile's (row tile's) table
+  static_assert(NW % CW == 0 && NW % RT == 0, "whole waves per column and row tile");
   constexpr bool kPixel = MODE != 1, kTrap = MODE <= 1;
   extern __shared__ float4 lds4[];
   const int b = blockIdx.z;
@@ -289,12 +289,12 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
   }
   const int Mp = (M + 15) & ~15;
   const int ntm = mc >> 4;
-  unsigned* xf = reinterpret_cast<unsigned*>(lds4);              // [CT][ntm] X fragments
-  unsigned* wf = xf + CT * ntm * kFragWords;                     // [RT][ntm] weighted Y fragments
+  unsigned* xf = reinterpret_cast<unsigned*>(lds4);              // [CW][ntm] X fragments
+  unsigned* wf = xf + CW * ntm * kFragWords;                     // [RT][ntm] weighted Y fragments
   float4* yf = reinterpret_cast<float4*>(wf + RT * ntm * kFragWords);  // [RT][ntm][2][64] Y, FP32
-  float4* refs = yf + RT * ntm * 128;                            // group constants {K, s, q}: [CT + RT][mc]
-  float4* sx = refs + (CT + RT) * mc;                            // KH > 1: [NW][CTW][2][64] partial pixel sums
-  float2* red = reinterpret_cast<float2*>(sx + (KH > 1 ? NW * CTW * 128 : 0));  // [NS][mc] trap sums
+  float4* refs = yf + RT * ntm * 128;                            // group constants {K, s, q}: [CW + RT][mc]
+  float4* sx = refs + (CW + RT) * mc;                            // KH > 1: [NW][2][64] partial pixel sums
+  float2* red = reinterpret_cast<float2*>(sx + (KH > 1 ? NW * 128 : 0));  // [NS][mc] trap sums
   float2* cw = red + NS * mc;                                    // [Mp] c_m
   float* sh = reinterpret_cast<float*>(cw + Mp);                 // [2 NW]
 
@@ -302,9 +302,9 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
   const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
   const int tw = wave % NS, part = wave / NS;    // the wave's pixels, and its share of the traps
   const int rt = tw / CW, cwv = tw - rt * CW;    // its row tile, and its group of column tiles
-  const int row0 = blockIdx.y * (16 * RT), cb = blockIdx.x * (16 * CT);
+  const int row0 = blockIdx.y * (16 * RT), cb = blockIdx.x * (16 * CW);
   const int r = row0 + 16 * rt + li;
-  const int c0 = cb + 16 * CTW * cwv + 4 * g;  // the lane's first column of its first tile
+  const int c0 = cb + 16 * cwv + 4 * g;  // the lane's first column
   const size_t pix0 = (size_t)b * nx * ny + (size_t)r * nx + c0;
 
   const int ewofs = 16 * g + kTqWords * (li >> 2) + (li & 3);  // entry (4 g + v, trap li): + 4 v
@@ -317,11 +317,11 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
   }
 
   // group constants of this wave's share of the tables, traps [k0, k0 + n): tile tx for the trap
-  // tiles wave / CT, + XS, ..., and row tile ty for wave / RT, + YS, ...; written and read by this
+  // tiles wave / CW, + XS, ..., and row tile ty for wave / RT, + YS, ...; written and read by this
   // wave alone
-  const int tx = wave % CT, ty = wave % RT, jx = wave / CT, jy = wave / RT;
+  const int tx = wave % CW, ty = wave % RT, jx = wave / CW, jy = wave / RT;
   float4* rx = refs + tx * mc;
-  float4* ry = refs + (CT + ty) * mc;
+  float4* ry = refs + (CW + ty) * mc;
   auto group = [&](const TrapCoef& k, double lin, double X) {
     const double kk = __builtin_fma(k.g, X * X, lin * X);
     double sl = __builtin_fma(4.0 * k.g, X, 2.0 * lin);
@@ -423,18 +423,18 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
     put_y(tt, e);
   }
 
-  u32x4 eh[CTW], el[CTW], fh[CTW], fl[CTW];  // E = (Er, Ei) hi, lo and (Ei, -Er) hi, lo
-  auto put_e = [&](int ct, const float* er, const float* ei) {
+  u32x4 eh, el, fh, fl;  // E = (Er, Ei) hi, lo and (Ei, -Er) hi, lo
+  auto put_e = [&](const float* er, const float* ei) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const Split s = split(er[v], ei[v]);
-      eh[ct][v] = s.hi;
-      el[ct][v] = s.lo;
-      fh[ct][v] = turn_m(s.hi);
-      fl[ct][v] = turn_m(s.lo);
+      eh[v] = s.hi;
+      el[v] = s.lo;
+      fh[v] = turn_m(s.hi);
+      fl[v] = turn_m(s.lo);
     }
   };
-  auto inside = [&](int ct, int v) { return r < ny && c0 + 16 * ct + v < nx; };
+  auto inside = [&](int v) { return r < ny && c0 + v < nx; };
 
   if constexpr (kPixel) {
     bool inf;
@@ -458,12 +458,7 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
       }
     }
 
-    f32x4 sre[CTW], sim[CTW];
-#pragma unroll
-    for (int ct = 0; ct < CTW; ++ct) {
-      sre[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      sim[ct] = sre[ct];
-    }
+    f32x4 sre = {0.0f, 0.0f, 0.0f, 0.0f}, sim = sre;
     for (int s = 0; s < nsc; ++s) {
       const int k0 = s * mc, n = min(mc, Mp - k0), nt = n >> 4;
       if (s > 0) rebuild(k0, n, true);
@@ -479,86 +474,63 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
           ch[v] = turn_p(bh[v]);
           cl[v] = turn_p(bl[v]);
         }
-#pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) {
-          const unsigned* xb = xf + ((cwv * CTW + ct) * ntm + tt) * kFragWords + pofs;
-          const u32x4 ah = *reinterpret_cast<const u32x4*>(xb), al = *reinterpret_cast<const u32x4*>(xb + kLoWords);
-          sre[ct] = mfma32(ah, bh, sre[ct]);
-          sim[ct] = mfma32(ah, ch, sim[ct]);
-          sre[ct] = mfma32(ah, bl, sre[ct]);
-          sim[ct] = mfma32(ah, cl, sim[ct]);
-          sre[ct] = mfma32(al, bh, sre[ct]);
-          sim[ct] = mfma32(al, ch, sim[ct]);
-        }
+        const unsigned* xb = xf + (cwv * ntm + tt) * kFragWords + pofs;
+        const u32x4 ah = *reinterpret_cast<const u32x4*>(xb), al = *reinterpret_cast<const u32x4*>(xb + kLoWords);
+        sre = mfma32(ah, bh, sre);
+        sim = mfma32(ah, ch, sim);
+        sre = mfma32(ah, bl, sre);
+        sim = mfma32(ah, cl, sim);
+        sre = mfma32(al, bh, sre);
+        sim = mfma32(al, ch, sim);
       }
     }
     if constexpr (KH > 1) {
-#pragma unroll
-      for (int ct = 0; ct < CTW; ++ct) {
-        float4* p = sx + (wave * CTW + ct) * 128 + lane;
-        p[0] = make_float4(sre[ct][0], sre[ct][1], sre[ct][2], sre[ct][3]);
-        p[64] = make_float4(sim[ct][0], sim[ct][1], sim[ct][2], sim[ct][3]);
-      }
+      float4* p = sx + wave * 128 + lane;
+      p[0] = make_float4(sre[0], sre[1], sre[2], sre[3]);
+      p[64] = make_float4(sim[0], sim[1], sim[2], sim[3]);
       __syncthreads();
 #pragma unroll
-      for (int ct = 0; ct < CTW; ++ct) {
-#pragma unroll
-        for (int k = 0; k < KH; ++k) {
-          const float4* p = sx + ((tw + k * NS) * CTW + ct) * 128 + lane;
-          const float4 a = p[0], c = p[64];
-          const f32x4 ra = {a.x, a.y, a.z, a.w}, ia = {c.x, c.y, c.z, c.w};
-          sre[ct] = k == 0 ? ra : sre[ct] + ra;
-          sim[ct] = k == 0 ? ia : sim[ct] + ia;
-        }
+      for (int k = 0; k < KH; ++k) {
+        const float4* p = sx + (tw + k * NS) * 128 + lane;
+        const float4 a = p[0], c = p[64];
+        const f32x4 ra = {a.x, a.y, a.z, a.w}, ia = {c.x, c.y, c.z, c.w};
+        sre = k == 0 ? ra : sre + ra;
+        sim = k == 0 ? ia : sim + ia;
       }
     }
     if constexpr (MODE == 3) {
 #pragma unroll
-      for (int ct = 0; ct < CTW; ++ct) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          if (inside(ct, v)) {
-            const size_t px = pix0 + 16 * ct + v;
-            const float pr = phase_turn(phase[px]);
-            grad[px] = __builtin_amdgcn_ldexpf(
-                inv_n * (__builtin_amdgcn_cosf(pr) * sim[ct][v] - __builtin_amdgcn_sinf(pr) * sre[ct][v]), wexp);
-          }
+      for (int v = 0; v < 4; ++v) {
+        if (inside(v)) {
+          const size_t px = pix0 + v;
+          const float pr = phase_turn(phase[px]);
+          grad[px] = __builtin_amdgcn_ldexpf(
+              inv_n * (__builtin_amdgcn_cosf(pr) * sim[v] - __builtin_amdgcn_sinf(pr) * sre[v]), wexp);
         }
       }
     } else {
       if (phase != nullptr && part == 0) {  // (the last mask of a solve)
 #pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (inside(ct, v)) phase[pix0 + 16 * ct + v] = inf ? __builtin_nanf("") : phase_of(sim[ct][v], sre[ct][v]);
-        }
+        for (int v = 0; v < 4; ++v)
+          if (inside(v)) phase[pix0 + v] = inf ? __builtin_nanf("") : phase_of(sim[v], sre[v]);
       }
       if constexpr (kTrap) {
+        float er[4], ei[4];
 #pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) {
-          float er[4], ei[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            unit_of(sre[ct][v], sim[ct][v], inside(ct, v), inf, er[v], ei[v]);
-          }
-          put_e(ct, er, ei);
-        }
+        for (int v = 0; v < 4; ++v) unit_of(sre[v], sim[v], inside(v), inf, er[v], ei[v]);
+        put_e(er, ei);
       }
     }
   } else {
+    float er[4], ei[4];
 #pragma unroll
-    for (int ct = 0; ct < CTW; ++ct) {
-      float er[4], ei[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const bool in = inside(ct, v);
-        const float2 u = unit_turn(in ? phase_turn(phase[pix0 + 16 * ct + v]) : 0.0f);
-        er[v] = in ? u.x : 0.0f;
-        ei[v] = in ? u.y : 0.0f;
-      }
-      put_e(ct, er, ei);
+    for (int v = 0; v < 4; ++v) {
+      const bool in = inside(v);
+      const float2 u = unit_turn(in ? phase_turn(phase[pix0 + v]) : 0.0f);
+      er[v] = in ? u.x : 0.0f;
+      ei[v] = in ? u.y : 0.0f;
     }
+    put_e(er, ei);
     __syncthreads();
   }
 
@@ -579,26 +551,20 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
           const int t = min(tt + p, t1 - 1);
           tre[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
           tim[p] = tre[p];
-          u32x4 xh[CTW];
+          const unsigned* xb = xf + (cwv * ntm + t) * kFragWords + ewofs;
+          u32x4 xh, xl;
 #pragma unroll
-          for (int ct = 0; ct < CTW; ++ct) {
-            const unsigned* xb = xf + ((cwv * CTW + ct) * ntm + t) * kFragWords + ewofs;
-            u32x4 xl;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              xh[ct][v] = xb[4 * v];
-              xl[v] = xb[4 * v + kLoWords];
-            }
-            tre[p] = mfma32(el[ct], xh[ct], tre[p]);
-            tim[p] = mfma32(fl[ct], xh[ct], tim[p]);
-            tre[p] = mfma32(eh[ct], xl, tre[p]);
-            tim[p] = mfma32(fh[ct], xl, tim[p]);
+          for (int v = 0; v < 4; ++v) {
+            xh[v] = xb[4 * v];
+            xl[v] = xb[4 * v + kLoWords];
           }
-#pragma unroll
-          for (int ct = 0; ct < CTW; ++ct) {  // (the large products last: every sum before them rounds finer)
-            tre[p] = mfma32(eh[ct], xh[ct], tre[p]);
-            tim[p] = mfma32(fh[ct], xh[ct], tim[p]);
-          }
+          tre[p] = mfma32(el, xh, tre[p]);
+          tim[p] = mfma32(fl, xh, tim[p]);
+          tre[p] = mfma32(eh, xl, tre[p]);
+          tim[p] = mfma32(fh, xl, tim[p]);
+          // (the large products last: every sum before them rounds finer)
+          tre[p] = mfma32(eh, xh, tre[p]);
+          tim[p] = mfma32(fh, xh, tim[p]);
         }
         float2 q[2];
 #pragma unroll
@@ -979,30 +945,30 @@ k_wide(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
   }
 }
 
-template <int RT, int CW, int CTW, int KH, int MODE>
+template <int RT, int CW, int KH, int MODE>
 hipError_t tile_t(hipStream_t s, const SepArgs& a) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile<RT, CW, CTW, KH, MODE>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile<RT, CW, KH, MODE>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax);
   if (attr != hipSuccess) return attr;
-  const TileShape sh{RT, CW, CTW, KH};
+  const TileShape sh{RT, CW, 1, KH};
   const size_t lds = tile_lds_bytes(sh, a.sc, a.mmax);
   if (lds > (size_t)kLdsMax) return hipErrorInvalidValue;
   if (MODE == 0 && (!a.acc_in || !a.acc_out || !a.acc_zero || a.T < 1)) return hipErrorInvalidValue;
   dim3 grid(sh.gx(a.nx), sh.gy(a.ny), a.B);
-  hipLaunchKernelGGL((k_tile<RT, CW, CTW, KH, MODE>), grid, dim3(sh.waves() * 64), lds, s, a.coef, a.st_in, a.acc_in,
+  hipLaunchKernelGGL((k_tile<RT, CW, KH, MODE>), grid, dim3(sh.waves() * 64), lds, s, a.coef, a.st_in, a.acc_in,
                      a.B == 1 ? a.one_m : 0, a.B == 1 ? a.one_off : 0, a.T, a.acc_unscale, a.nx, a.ny, a.sc, a.upd,
                      a.hd, a.st_out, a.vin, a.hist, a.flag, a.inv_n, a.phase, a.grad, a.partial, a.acc_out, a.acc_zero,
                      a.acc_scale);
   return hipGetLastError();
 }
 
-template <int RT, int CW, int CTW, int KH>
+template <int RT, int CW, int KH>
 hipError_t tile_mode(hipStream_t s, const SepArgs& a) {
   switch (a.mode) {
-    case 0: return tile_t<RT, CW, CTW, KH, 0>(s, a);
-    case 1: return tile_t<RT, CW, CTW, KH, 1>(s, a);
-    case 2: return tile_t<RT, CW, CTW, KH, 2>(s, a);
-    case 3: return tile_t<RT, CW, CTW, KH, 3>(s, a);
+    case 0: return tile_t<RT, CW, KH, 0>(s, a);
+    case 1: return tile_t<RT, CW, KH, 1>(s, a);
+    case 2: return tile_t<RT, CW, KH, 2>(s, a);
+    case 3: return tile_t<RT, CW, KH, 3>(s, a);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1044,8 +1010,8 @@ hipError_t launch_tile(hipStream_t s, const SepArgs& a) {
   if (a.nx < 1 || a.ny < 1 || a.mmax < 1 || a.mmax > kMaxTraps || a.sc < 16 || a.sc % 16 != 0)
     return hipErrorInvalidValue;
   switch (a.shape) {
-    case kTile32: return tile_mode<2, 2, 1, 1>(s, a);
-    case kTile32Split: return tile_mode<2, 2, 1, 2>(s, a);
+    case kTile32: return tile_mode<2, 2, 1>(s, a);
+    case kTile32Split: return tile_mode<2, 2, 2>(s, a);
     case kTileWide: return wide_mode(s, a);
     default: return hipErrorInvalidValue;
   }
