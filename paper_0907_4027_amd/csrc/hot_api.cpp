@@ -352,7 +352,7 @@ bool use_tiles(const hot_ctx* c, int variant, Job job, int nx, int ny, int B, in
 //   than 48 traps on a grid of at most one block per unit, where a second wave per SIMD hides latency
 //   (512^2 x 100: 7.5 against 8.2 us); with fewer traps or two resident blocks the exchange of the
 //   partial sums costs more than it hides (641 x 479 x 37: 12.8 against 12.4 us).  (All of these with
-//   unpadded regions of the trap sums; acc_stride took the 7.5 us to 6.9.)
+//   unpadded regions of the trap sums; acc_stride took 0.3 us off a launch of 512^2 x 100.)
 // All traps at once where their tables fit the LDS (up to 256 in k_wide); on a grid of more blocks than
 // units half of the LDS, so that two blocks share a unit and one's vector work overlaps the other's
 // matrix products (k_wide's comment has both sides).

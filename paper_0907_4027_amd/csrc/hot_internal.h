@@ -96,10 +96,10 @@ struct FwdGeom {
 // such buffers rotate over the iterations.
 constexpr int kAccRegions = 8;
 // Words from one region to the next: whole cache lines of 128 bytes, so that no line is added to by
-// two XCDs, whose L2s would take it from each other: GSW 512^2 x 100 took 7.4 us per launch with regions
-// of exactly T words, 7.1 with these (any T that is not a multiple of 16).  16 or 32 regions (each XCD's
-// blocks over two or four) shorten the queue of adds to a word further, but the next launch then waits
-// longer for V: 7.0 us here, and 256^2 x 16 180 -> 186 us a solve, 1024^2 x 256 746 -> 753.
+// two XCDs, whose L2s would take it from each other: GSW 512^2 x 100, 50 iterations, took 379 us with
+// regions of exactly T words, 363 with these (0.3 us per launch; any T that is not a multiple of 16).  16 or
+// 32 regions (each XCD's blocks over two or four) shorten the queue of adds to a word further, but the next
+// launch then waits longer for V: 358 us here, and 256^2 x 16 180 -> 186 us a solve, 1024^2 x 256 746 -> 753.
 inline int acc_stride(int T) { return (T + 15) & ~15; }
 
 struct IterArgs {

@@ -4,8 +4,10 @@ Per frame: the traps move (the caller passes their new positions), a few GSW
 iterations run warm-started from the previous frame's weights and trap phases,
 the phase mask is encoded as the 8-bit SLM frame (grey level linear in phase
 over 0..2 pi), and the frame is copied into pinned host memory, where a display
-path would pick it up.  All device work goes through the C ABI; buffers are
-fixed, so every frame after the first replays the same captured graph.
+path would pick it up.  All device work goes through the C ABI, in buffers that
+are fixed from the first frame on; with more iterations per frame than the
+library launches one by one (24), every frame after the first replays the same
+captured graph.
 """
 from __future__ import annotations
 
