@@ -227,7 +227,7 @@ int hot_forward_V(hot_ctx* ctx, const hot_slm* slm, int32_t B, const int32_t* M,
 
 /* Adjoint of Eq. 1: for a real loss L(V) and G_m = dL/dRe V_m + i dL/dIm V_m (device, 2T),
  *   grad_phase[b][j] = dL/dphi_j = (1/N) Im( exp(-i phi_j) sum_m G_m exp(i Delta_j^m) ),
- * with Delta recomputed (never stored).  phase device B x N, grad_phase device B x N.
+ * with Delta recomputed (never stored).  phase device B x N, grad_phase device B x N (may be phase).
  * A G_m that is not finite makes its hologram's whole gradient non-finite, and no other's. */
 int hot_adjoint(hot_ctx* ctx, const hot_slm* slm, int32_t B, const int32_t* M, const double* xyz,
                 const float* phase, const float* G, float* grad_phase);

@@ -499,9 +499,10 @@ k_tile(const TrapCoef* __restrict__ coef, const TrapState* __restrict__ st_in,
       }
     }
     if constexpr (MODE == 3) {
+      // (each pixel by one wave alone, which reads its phase before it writes: grad may be phase itself)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        if (inside(v)) {
+        if (inside(v) && v * KH / 4 == part) {
           const size_t px = pix0 + v;
           const float pr = phase_turn(phase[px]);
           grad[px] = __builtin_amdgcn_ldexpf(

@@ -270,3 +270,21 @@ def test_fields_and_gradients_of_widely_spread_weights(hot, decades):
     assert np.abs(as_complex(to_np(r.V)) - oracle.forward(p.slm, p.xyz, mask)).max() <= 2e-6
     ref = oracle.adjoint(p.slm, p.xyz, phi.ravel().astype(np.float64), G[:, 0].astype(np.float64) + 1j * G[:, 1])
     assert relative(g.ravel(), np.ravel(ref)) <= 2e-6
+
+
+@pytest.mark.parametrize("nx,ny,m", [(70, 40, 20), (96, 64, 60), (512, 300, 100), (700, 840, 20)])
+@pytest.mark.parametrize("variant,knobs", [("onthefly", {}), ("onthefly", {"rows": 1}), ("separable", {"sep_waves": 1})])
+def test_adjoint_in_place(hot, nx, ny, m, variant, knobs):
+    """The gradient may be written over the phase it is taken at: every pixel's phase is read once, by the
+    wave that writes its gradient (two waves share the traps of a tile in the second and third case)."""
+    slm, rng = W.Slm(nx, ny), np.random.default_rng(m)
+    xyz = W.box_uniform(rng, m)
+    phi = torch.tensor(rng.uniform(0.0, 6.0, (1, ny, nx)), dtype=torch.float32, device="cuda")
+    G = torch.tensor(rng.standard_normal((m, 2)), dtype=torch.float32, device="cuda")
+    with hot.Context(0) as c:
+        c.set_variant(variant)
+        c.set_tuning(**knobs)
+        ref = c.hot_adjoint(slm, [m], xyz, phi, G)
+        for _ in range(3):
+            x = phi.clone()
+            assert torch.equal(c.hot_adjoint(slm, [m], xyz, x, G, grad=x), ref)
