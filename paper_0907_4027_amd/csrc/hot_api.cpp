@@ -312,6 +312,15 @@ FwdGeom row_segments(int nx, int ny, int segmax) {
   return f;
 }
 
+int64_t tile_blocks(int shape, int nx, int ny, int B) {
+  return (int64_t)kTileShapes[shape].gx(nx) * kTileShapes[shape].gy(ny) * B;
+}
+
+// Whether the tile kernels' blocks are of 64 x 64 pixels (choose_tile has the reasons).
+bool wide_tiles(const hot_ctx* c, int nx, int ny, int B) {
+  return 2 * tile_blocks(kTileWide, nx, ny, B) >= c->num_cu && tile_blocks(kTile32, nx, ny, B) > c->num_cu;
+}
+
 // What a call computes, where the choice of kernels depends on it.
 enum class Job { kSolve, kField, kAdjoint };
 
@@ -347,7 +356,9 @@ bool use_tiles(const hot_ctx* c, int variant, Job job, int nx, int ny, int B, in
 //   64 x 64 pixels (k_wide) once such blocks number at least half of the compute units: per pixel they
 //   build half of the table entries of 32 x 32 blocks (GSW 1024^2 x 256: 18.5 against 42.7 us per
 //   iteration; 768^2 x 81, 144 blocks: 13 against 20.5 us), while a grid with fewer leaves units idle
-//   (641 x 479 x 37, 88 blocks: 13.2 against 12.4 us; 512^2 x 100, 64 blocks: 12.2 against 7.5 us).
+//   (641 x 479 x 37, 88 blocks: 13.2 against 12.4 us; 512^2 x 100, 64 blocks: 12.2 against 7.5 us), as do
+//   half-empty ones where 32 x 32 blocks still find a unit each (2 holograms of 4096 x 16 x 100, 30
+//   iterations, 128 or 256 blocks: 347 against 231 us, x 512 1175 against 678).
 //   Else 32 x 32: four waves, or eight (two sharing each 16 x 16 tile, half of the traps each) for more
 //   than 48 traps on a grid of at most one block per unit, where a second wave per SIMD hides latency
 //   (512^2 x 100: 7.5 against 8.2 us); with fewer traps or two resident blocks the exchange of the
@@ -357,8 +368,8 @@ bool use_tiles(const hot_ctx* c, int variant, Job job, int nx, int ny, int B, in
 // units half of the LDS, so that two blocks share a unit and one's vector work overlaps the other's
 // matrix products (k_wide's comment has both sides).
 void choose_tile(const hot_ctx* c, Plan& P) {
-  auto blocks = [&](int shape) { return (int64_t)kTileShapes[shape].gx(P.nx) * kTileShapes[shape].gy(P.ny) * P.B; };
-  const bool wide = 2 * blocks(kTileWide) >= c->num_cu;
+  auto blocks = [&](int shape) { return tile_blocks(shape, P.nx, P.ny, P.B); };
+  const bool wide = wide_tiles(c, P.nx, P.ny, P.B);
   P.tile = wide ? kTileWide : P.mmax > 48 && blocks(kTile32) <= c->num_cu ? kTile32Split : kTile32;
   const TileShape& t = kTileShapes[P.tile];
   P.nblk_tile = t.gx(P.nx) * t.gy(P.ny);

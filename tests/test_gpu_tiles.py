@@ -288,3 +288,18 @@ def test_adjoint_in_place(hot, nx, ny, m, variant, knobs):
         for _ in range(3):
             x = phi.clone()
             assert torch.equal(c.hot_adjoint(slm, [m], xyz, x, G, grad=x), ref)
+
+
+@pytest.mark.parametrize("b,nx,ny,m", [(2, 4096, 16, 50), (4, 32, 2048, 20), (2, 4096, 33, 20)])
+def test_half_empty_grids(hot, b, nx, ny, m):
+    """As many 64 x 64 blocks as half of the units: masks of up to 32 rows or columns take 32 x 32 ones."""
+    rng = np.random.default_rng(ny)
+    slm, T = W.Slm(nx, ny), b * m
+    xyz, theta0 = W.box_uniform(rng, T), rng.uniform(0.0, 2.0 * np.pi, T)
+    with hot.Context(0) as c:
+        r = c.hot_gsw_batched(slm, [m] * b, xyz, theta0, 2)
+    for i in range(b):
+        s = slice(i * m, i * m + m)
+        o = oracle.solve("gsw", slm, xyz[s], theta0[s], 2)
+        assert_phase(to_np(r.phase[i]), o["phi"])
+        assert_V(to_np(r.V[s]), o["V"])
