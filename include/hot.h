@@ -113,8 +113,8 @@ int hot_set_variant(hot_ctx* ctx, int variant);
 /* Launch-shape knobs (used by the autotuner; 0 restores the built-in choice, except
  * HOT_TUNE_GRAPHS).  They change how work is tiled or launched, never what is computed
  * beyond FP32 rounding.  With every knob of a variant at 0 it runs on the tile kernels, which choose
- * their own shapes (but for hundreds of traps on masks of a few thousand pixels, where the direct sums of
- * the on-the-fly variant are faster); a HOT_TUNE_SEP knob selects the FP32 matrix kernels of the separable variant, any
+ * their own shapes (but for batches of masks of a few rows and for hundreds of traps on masks of a few thousand
+ * pixels, where the direct sums of the on-the-fly variant are faster); a HOT_TUNE_SEP knob selects the FP32 matrix kernels of the separable variant, any
  * other knob (but HOT_TUNE_GRAPHS) the direct-sum kernels of the on-the-fly variant, and the built-in
  * choices named below are those kernels' own. */
 enum hot_tuning_key {

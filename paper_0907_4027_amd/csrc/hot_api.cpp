@@ -322,13 +322,35 @@ bool wide_tiles(const hot_ctx* c, int nx, int ny, int B) {
 }
 
 // What a call computes, where the choice of kernels depends on it.
-enum class Job { kSolve, kField, kAdjoint };
+struct Job {
+  enum Kind { kSolve, kField, kAdjoint } kind;
+  int iters = 0;  // kSolve: iterations
+};
+
+// Whether a batch of thin masks is faster on the direct sums.  A 16 x 16 tile of the matrix products takes
+// its time however few of its rows exist, and 64 x 64 blocks leave most of theirs empty on masks of a few
+// rows; the direct sums have a block per row and 512 columns, but spend host time on each hologram's lane
+// layout.  Microseconds per launch and per call, fitted to 3600 batches of 1..48 rows, 300..4096 columns,
+// 1..512 traps and 0..50 iterations on 256 units (the wrong side of the line costs 1.02 times on average
+// there and 1.4 at most; without it the tile kernels take up to 5.8 times as long).  Per solve, direct
+// against tile kernels: 64 of 4096 x 1 with 64 traps and 50 iterations 752 against 3909, 17 of 4096 x 6 x 100,
+// 30 iterations 793 against 1173, 32 of 4096 x 1 x 512, 5 iterations 341 against 1519; 17 of 1024 x 24 x 32,
+// 50 iterations 729 against 468, 17 of 1024 x 3 x 100, 2 iterations 122 against 90 (host).
+bool thin_batch(const hot_ctx* c, int nx, int ny, int B, int T, int iters) {
+  if (B == 1 || !wide_tiles(c, nx, ny, B)) return false;
+  const double wide = (double)tile_blocks(kTileWide, nx, ny, B);
+  const double rows = (double)B * ((nx + 511) / 512) * ny, m = (double)T / B, mp = 16.0 * std::ceil(m / 16.0);
+  const double tile = wide <= c->num_cu ? 3.5 + 0.066 * mp : std::max(4.8 + 0.1 * mp, 1e-3 * wide * (10.0 + 0.22 * mp));
+  const double direct = std::max(4.6 + 0.062 * m, 1e-3 * rows * (3.9 + 0.27 * m));
+  return direct < tile && 33.0 + 6.4 * B < tile * (iters + 1);
+}
 
 // Whether the on-the-fly or separable variant runs on the tile kernels.  A launch-shape knob of that
 // variant's other kernels (the direct-sum kernels' for the on-the-fly variant, the FP32 matrix kernels'
-// for the separable one) selects those.  Else always, but for very many traps on small masks: a block of
-// the tile kernels then works off its traps one super-chunk after the other, on a few compute units of
-// the chip, while the direct sums have a block per row.
+// for the separable one) selects those.  Else always, but in the on-the-fly variant for batches of thin
+// masks (above) and for very many traps on small masks: a block of the tile kernels then works off its traps
+// one super-chunk after the other, on a few compute units of the chip, while the direct sums have a block
+// per row.
 //   Solves: a row's time grows with its length, so the line lies at ten traps per column (direct against
 //   tile kernels, us per GSW solve of 5 / 40 iterations: 16^2 x 1024 222 / 1410 against 251 / 1664,
 //   64^2 x 1024 240 / 1540 against 257 / 1705, 96 x 80 x 1024 253 / 1624 against 258 / 1715, 128^2 x 1024
@@ -341,13 +363,14 @@ enum class Job { kSolve, kField, kAdjoint };
 //   against 43.9).  For several masks the search for the lane layouts, on the host, costs more than the
 //   sums save (4 of 64^2 x 2048 65 against 49).
 // The adjoint is faster on the tile kernels throughout (64^2 x 2048 37 against 49).
-bool use_tiles(const hot_ctx* c, int variant, Job job, int nx, int ny, int B, int mmax) {
+bool use_tiles(const hot_ctx* c, int variant, Job job, int nx, int ny, int B, int T, int mmax) {
   if (variant == HOT_STORED) return false;
   if (variant == HOT_SEPARABLE) return !c->tune_sepw && !c->tune_sepc && !c->tune_sepk;
   if (c->tune_q || c->tune_tpl || c->tune_seg || c->tune_amax || c->tune_rows || c->tune_fract) return false;
-  if (job == Job::kSolve)
-    return !(mmax >= 512 && mmax >= 10 * nx && nx <= 128 && (int64_t)ny * B <= c->num_cu);
-  if (job == Job::kField)
+  if (job.kind == Job::kSolve)
+    return !(mmax >= 512 && mmax >= 10 * nx && nx <= 128 && (int64_t)ny * B <= c->num_cu) &&
+           !thin_batch(c, nx, ny, B, T, job.iters);
+  if (job.kind == Job::kField)
     return !(B == 1 && mmax > 896 && 4 * (int64_t)row_segments(nx, ny, kSpan).nblk() <= 3 * c->num_cu);
   return true;
 }
@@ -407,7 +430,7 @@ int prepare_into(hot_ctx* c, int variant, Job job, const hot_slm* slm, int B, co
     P.T += counts[b];
     P.mmax = std::max(P.mmax, (int)counts[b]);
   }
-  P.tiles = use_tiles(c, variant, job, P.nx, P.ny, B, P.mmax);
+  P.tiles = use_tiles(c, variant, job, P.nx, P.ny, B, P.T, P.mmax);
   // fused kernel shape
   {
     const int q = c->tune_q == 2 ? 2 : 1;
@@ -743,7 +766,7 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   int rc;
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, variant, Job::kSolve, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
+  if ((rc = prepare(c, variant, {Job::kSolve, algo == kRS ? 0 : iters}, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
   const int K = algo == kRS ? 0 : iters;
   const bool stored = variant == HOT_STORED;
   const bool separable = variant == HOT_SEPARABLE;
@@ -1176,7 +1199,7 @@ int hot_gsw_noalloc(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
     c->na_pending = false;
   }
   Plan P;
-  if ((rc = prepare_into(c, HOT_ONTHEFLY, Job::kSolve, slm, 1, &M, xyz, theta0, theta0 == nullptr, seed, P,
+  if ((rc = prepare_into(c, HOT_ONTHEFLY, {Job::kSolve, iters}, slm, 1, &M, xyz, theta0, theta0 == nullptr, seed, P,
                          (TrapCoef*)(c->na_host + L.coef), (TrapState*)(c->na_host + L.st), (HoloDesc*)(c->na_host + L.hd))))
     return rc;
   char* base = (char*)c->scratch;
@@ -1340,7 +1363,7 @@ int hot_forward_V(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M, c
   if ((rc = set_dev(c))) return rc;
   Plan P;
   std::vector<double> zeros(T, 0.0);
-  if ((rc = prepare(c, fa_variant(c), Job::kField, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
+  if ((rc = prepare(c, fa_variant(c), {Job::kField}, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, M, false))) return rc;
   if (P.tiles) {
     if ((rc = ensure(c, c->partial, sizeof(float2) * (size_t)P.T * P.nblk_tile))) return rc;
@@ -1377,7 +1400,7 @@ int hot_adjoint(hot_ctx* c, const hot_slm* slm, int32_t B, const int32_t* M, con
   if ((rc = set_dev(c))) return rc;
   Plan P;
   std::vector<double> zeros(T, 0.0);
-  if ((rc = prepare(c, fa_variant(c), Job::kAdjoint, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
+  if ((rc = prepare(c, fa_variant(c), {Job::kAdjoint}, slm, B, M, xyz, zeros.data(), false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, M, false))) return rc;
   if (P.tiles) {
     SepArgs a = tile_args(c, P, 3, const_cast<float*>(phase), 0);
@@ -1418,7 +1441,7 @@ int hot_time_passes(hot_ctx* c, const hot_slm* slm, int32_t M, const double* xyz
   if (reps < 1) return fail(HOT_EINVAL, "reps = %d < 1", reps);
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, c->variant, Job::kSolve, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
+  if ((rc = prepare(c, c->variant, {Job::kSolve}, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
   const bool stored = c->variant == HOT_STORED;
   const bool separable = c->variant == HOT_SEPARABLE;
   const bool tiles = P.tiles;
@@ -1552,7 +1575,7 @@ int hot_pixel_pass_variant(hot_ctx* c, const hot_slm* slm, int32_t M, const doub
   if (reps < 1) return fail(HOT_EINVAL, "reps = %d < 1", reps);
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, HOT_ONTHEFLY, Job::kSolve, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
+  if ((rc = prepare(c, HOT_ONTHEFLY, {Job::kSolve}, slm, 1, &M, xyz, theta0, false, 0, P))) return rc;
   if ((rc = upload_tables(c, slm, P, xyz, &M))) return rc;
   const int nb = abl_blocks(mapping, block, slm->nx, slm->ny);
   if ((rc = ensure(c, c->abl, sizeof(float4) * (size_t)nb * M))) return rc;

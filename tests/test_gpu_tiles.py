@@ -290,6 +290,29 @@ def test_adjoint_in_place(hot, nx, ny, m, variant, knobs):
             assert torch.equal(c.hot_adjoint(slm, [m], xyz, x, G, grad=x), ref)
 
 
+@pytest.mark.parametrize("nx,ny,counts,iters,direct", [(1500, 2, [100] * 12, 40, True), (4096, 1, [8, 20, 3] * 3, 30, True),
+                                                       (4096, 1, [8, 20, 3], 30, False), (640, 3, [260] * 20, 9, True),
+                                                       (1500, 2, [100] * 12, 0, False), (1024, 40, [30] * 16, 30, False)])
+def test_batches_of_thin_masks(hot, nx, ny, counts, iters, direct):
+    """Batches of masks of a few rows run on the direct sums (same bits as with a knob that selects them and
+    is their default); either side of the line matches the oracle."""
+    rng = np.random.default_rng(nx + ny)
+    slm, T = W.Slm(nx, ny), sum(counts)
+    xyz, theta0 = W.box_uniform(rng, T), rng.uniform(0.0, 2.0 * np.pi, T)
+    with hot.Context(0) as c, hot.Context(0) as k:
+        k.set_tuning(rows=1)
+        a, b = (x.hot_gsw_batched(slm, counts, xyz, theta0, iters) for x in (c, k))
+        r = c.hot_gsw_batched(slm, counts, xyz, theta0, 0)
+        torch.cuda.synchronize()
+    assert torch.equal(a.phase, b.phase) == direct
+    o = 0
+    for i, m in enumerate(counts[:3]):
+        ref = oracle.backward(slm, xyz[o:o + m], None, theta0[o:o + m])
+        assert_phase(to_np(r.phase[i]), ref)
+        assert np.abs(as_complex(to_np(r.V[o:o + m])) - oracle.forward(slm, xyz[o:o + m], ref)).max() <= 5e-6
+        o += m
+
+
 @pytest.mark.parametrize("b,nx,ny,m", [(2, 4096, 16, 50), (4, 32, 2048, 20), (2, 4096, 33, 20)])
 def test_half_empty_grids(hot, b, nx, ny, m):
     """As many 64 x 64 blocks as half of the units: masks of up to 32 rows or columns take 32 x 32 ones."""
