@@ -766,8 +766,8 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
   int rc;
   if ((rc = set_dev(c))) return rc;
   Plan P;
-  if ((rc = prepare(c, variant, {Job::kSolve, algo == kRS ? 0 : iters}, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
   const int K = algo == kRS ? 0 : iters;
+  if ((rc = prepare(c, variant, {Job::kSolve, K}, slm, B, counts, xyz, theta0, seeded, seed, P))) return rc;
   const bool stored = variant == HOT_STORED;
   const bool separable = variant == HOT_SEPARABLE;
   const bool tiles = P.tiles;
@@ -882,15 +882,15 @@ int solve(hot_ctx* c, const hot_slm* slm, int B, const int32_t* counts, const do
     // everything a launch of the sequence is made of that may differ between calls: the largest trap
     // count too, which sets the dynamic LDS and strides of a batch's launches (each hologram's own count
     // is read on the device)
-    std::vector<uint64_t> key = {(uint64_t)B, (uint64_t)P.T, (uint64_t)P.mmax, (uint64_t)P.nx, (uint64_t)P.ny, (uint64_t)K,
-                                 (uint64_t)algo, (uint64_t)variant, (uint64_t)P.fract, (uint64_t)P.nt, (uint64_t)P.q,
-                                 (uint64_t)P.tpl, (uint64_t)P.fg.seg_w, (uint64_t)P.sep_w, (uint64_t)P.sep_sc, (uint64_t)P.sep_kh,
-                                 (uint64_t)P.rows, (uint64_t)tiles, (uint64_t)want, (uint64_t)(uintptr_t)c->hist.p, (uint64_t)P.tile, (uint64_t)P.tile_occ, (uint64_t)P.tile_mc, (uint64_t)(uintptr_t)phase,
-                                 (uint64_t)(uintptr_t)V, (uint64_t)(uintptr_t)w_out, (uint64_t)(uintptr_t)theta_out,
-                                 (uint64_t)(uintptr_t)c->coef.p, (uint64_t)(uintptr_t)c->st.p,
-                                 (uint64_t)(uintptr_t)c->hd.p, (uint64_t)(uintptr_t)c->partial.p,
-                                 (uint64_t)(uintptr_t)dstats, (uint64_t)(uintptr_t)c->amat.p,
-                                 (uint64_t)(uintptr_t)c->efield.p, (uint64_t)(uintptr_t)c->acc.p};
+    std::vector<uint64_t> key = {
+        (uint64_t)B, (uint64_t)P.T, (uint64_t)P.mmax, (uint64_t)P.nx, (uint64_t)P.ny, (uint64_t)K, (uint64_t)algo,
+        (uint64_t)variant, (uint64_t)P.fract, (uint64_t)P.nt, (uint64_t)P.q, (uint64_t)P.tpl, (uint64_t)P.fg.seg_w,
+        (uint64_t)P.sep_w, (uint64_t)P.sep_sc, (uint64_t)P.sep_kh, (uint64_t)P.rows, (uint64_t)tiles, (uint64_t)want,
+        (uint64_t)P.tile, (uint64_t)P.tile_occ, (uint64_t)P.tile_mc, (uint64_t)(uintptr_t)c->hist.p,
+        (uint64_t)(uintptr_t)phase, (uint64_t)(uintptr_t)V, (uint64_t)(uintptr_t)w_out, (uint64_t)(uintptr_t)theta_out,
+        (uint64_t)(uintptr_t)c->coef.p, (uint64_t)(uintptr_t)c->st.p, (uint64_t)(uintptr_t)c->hd.p,
+        (uint64_t)(uintptr_t)c->partial.p, (uint64_t)(uintptr_t)dstats, (uint64_t)(uintptr_t)c->amat.p,
+        (uint64_t)(uintptr_t)c->efield.p, (uint64_t)(uintptr_t)c->acc.p};
     hot_ctx::GraphEntry* hit = nullptr;
     for (auto& g : c->graphs)
       if (g.key == key) hit = &g;
